@@ -3,16 +3,18 @@
 //
 // Cuts: for a feature with sorted non-missing sketch values s_0..s_{N-1}
 // and B = max_bin, candidate k = s[ceil(kN/B)-1] (k = 1..B-1), duplicates
-// and values >= s_{N-1} dropped.  The order statistics are found on the GPU
-// by a multi-way bisection over order-preserving 32-bit keys: each pass
-// splits every unresolved target's key interval into 16 parts and counts,
-// per feature, the keys at or below every split point (LDS counters, one
-// binary search per key).  Eight passes resolve 32 bits.  The host only
-// narrows the intervals from the tiny count tables.
+// and values >= s_{N-1} dropped.  The order statistics are selected on the
+// GPU (cuts.hip).  Where its workspace does not fit the context's budget, a
+// multi-way bisection over the order-preserving 32-bit keys finds them
+// instead: each pass splits every unresolved target's key interval into 16
+// parts and counts, per feature, the keys at or below every split point (LDS
+// counters, one binary search per key), eight passes resolve 32 bits, and
+// the host narrows the intervals from the count tables.
 //
 // Pages: row-major rows of row_words 32-bit words; a row is the LSB-first
 // bit stream of its stride symbols (w bits each), zero padded.
 #include "common.h"
+#include "cuts_impl.h"
 #include "hist_impl.h"
 #include "sketch_impl.h"
 
@@ -634,62 +636,13 @@ static gbt_status finalize_merged(gbt_quantizer *q, const unsigned long long *st
     return finish_cuts(q, std::move(cut_ptr_h), std::move(cut_values_h), std::move(feat_count), stv);
 }
 
-gbt_status gbt_quantize_finalize_cuts(gbt_quantizer *q)
+// The order statistics of select_cut_keys by the bisection described at the
+// top, whose workspace is a few words per split point: for a context whose
+// byte budget has no room for the selection's workspace.
+static gbt_status bisect_cut_keys(gbt_ctx *c, const uint32_t *keys, const std::vector<int64_t> &seg, int32_t B,
+                                  std::vector<uint32_t> *vals, std::vector<int64_t> *N_out)
 {
-    GBT_CHECK(q, "quantizer is NULL");
-    GBT_CHECK(!q->cuts_done, "finalize_cuts called twice");
-    GBT_CHECK(q->sketched_rows == q->n_total, "sketched %lld of %lld rows",
-              (long long)q->sketched_rows, (long long)q->n_total);
-    gbt_ctx *c = q->ctx;
-    GBT_TRY(set_device(c));
-    const int32_t m = q->m, B = q->p.max_bin;
-    unsigned long long stv[kStWords];
-    GBT_TRY(read_status(q, stv));
-    if (q->ms) {
-        GBT_CHECK(!stv[kStInf], "input holds an infinite value");
-        return finalize_merged(q, stv);
-    }
-
-    // per-feature key segments
-    std::vector<int64_t> seg(m + 1, 0);
-    std::vector<int64_t> feat_count;  // CSR: present values per feature in the sketch rows
-    uint32_t *keys = q->keys;
-    uint32_t *sorted = nullptr;
-    size_t sorted_bytes = 0;
-    if (q->kind == GBT_INPUT_DENSE_F32) {
-        for (int32_t j = 0; j <= m; ++j) seg[j] = (int64_t)j * q->n_sketch;
-    } else {
-        int64_t nk = (int64_t)stv[kStKeys];
-        unsigned long long *cnt = nullptr;
-        GBT_TRY(dev_alloc(c, (size_t)(m + 1) * 8, (void **)&cnt));
-        std::vector<unsigned long long> h(m + 1, 0ull);
-        GBT_HIP(hipMemcpyAsync(cnt, h.data(), (m + 1) * 8, hipMemcpyHostToDevice, c->stream));
-        if (nk) {
-            k_feat_count<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, nk, cnt);
-            GBT_LAUNCHED();
-        }
-        GBT_HIP(hipMemcpyAsync(h.data(), cnt, m * 8, hipMemcpyDeviceToHost, c->stream));
-        GBT_HIP(hipStreamSynchronize(c->stream));
-        for (int32_t j = 0; j < m; ++j) seg[j + 1] = seg[j] + (int64_t)h[j];
-        feat_count.assign(h.begin(), h.begin() + m);
-        std::vector<unsigned long long> cur(m);
-        for (int32_t j = 0; j < m; ++j) cur[j] = (unsigned long long)seg[j];
-        GBT_HIP(hipMemcpyAsync(cnt, cur.data(), m * 8, hipMemcpyHostToDevice, c->stream));
-        sorted_bytes = (size_t)std::max<int64_t>(nk, 1) * 4;
-        gbt_status s = dev_alloc(c, sorted_bytes, (void **)&sorted);
-        if (s != GBT_OK) {
-            dev_free(c, cnt, (size_t)(m + 1) * 8);
-            return s;
-        }
-        if (nk) {
-            k_feat_scatter<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, q->keys, nk, cnt, sorted);
-            GBT_LAUNCHED();
-        }
-        GBT_HIP(hipStreamSynchronize(c->stream));
-        dev_free(c, cnt, (size_t)(m + 1) * 8);
-        keys = sorted;
-    }
-
+    const int32_t m = (int32_t)seg.size() - 1;
     // work items: chunks of each feature's segment
     const int64_t kChunk = 1 << 16;
     std::vector<CountWork> work;
@@ -698,7 +651,8 @@ gbt_status gbt_quantize_finalize_cuts(gbt_quantizer *q)
             work.push_back({b, std::min(seg[j + 1], b + kChunk), j, 0});
 
     // targets per feature: ranks ceil(kN/B)-1 (k=1..B-1) and N-1 (the maximum)
-    std::vector<int64_t> N(m, 0);
+    N_out->assign(m, 0);
+    std::vector<int64_t> &N = *N_out;
     std::vector<std::vector<int64_t>> rank(m);
     std::vector<std::vector<uint32_t>> lo(m), hi(m);
 
@@ -716,7 +670,6 @@ gbt_status gbt_quantize_finalize_cuts(gbt_quantizer *q)
         dev_free(c, boff_d, (size_t)(m + 1) * 4);
         dev_free(c, bounds_d, bcap * 4);
         dev_free(c, cnt_d, bcap * 4);
-        dev_free(c, sorted, sorted_bytes);
     };
     if (status != GBT_OK) {
         cleanup();
@@ -846,19 +799,91 @@ gbt_status gbt_quantize_finalize_cuts(gbt_quantizer *q)
         }
     }
     cleanup();
+    vals->assign((size_t)m * B, 0u);
+    for (int32_t j = 0; j < m; ++j) {
+        if (N[j] == 0) continue;
+        GBT_CHECK(lo[j].back() == hi[j].back(), "cut search did not converge");
+        std::copy(lo[j].begin(), lo[j].end(), vals->begin() + (size_t)j * B);
+    }
+    return GBT_OK;
+}
+
+gbt_status gbt_quantize_finalize_cuts(gbt_quantizer *q)
+{
+    GBT_CHECK(q, "quantizer is NULL");
+    GBT_CHECK(!q->cuts_done, "finalize_cuts called twice");
+    GBT_CHECK(q->sketched_rows == q->n_total, "sketched %lld of %lld rows",
+              (long long)q->sketched_rows, (long long)q->n_total);
+    gbt_ctx *c = q->ctx;
+    GBT_TRY(set_device(c));
+    const int32_t m = q->m, B = q->p.max_bin;
+    unsigned long long stv[kStWords];
+    GBT_TRY(read_status(q, stv));
+    if (q->ms) {
+        GBT_CHECK(!stv[kStInf], "input holds an infinite value");
+        return finalize_merged(q, stv);
+    }
+
+    // per-feature key segments
+    std::vector<int64_t> seg(m + 1, 0);
+    std::vector<int64_t> feat_count;  // CSR: present values per feature in the sketch rows
+    uint32_t *keys = q->keys;
+    uint32_t *sorted = nullptr;
+    size_t sorted_bytes = 0;
+    if (q->kind == GBT_INPUT_DENSE_F32) {
+        for (int32_t j = 0; j <= m; ++j) seg[j] = (int64_t)j * q->n_sketch;
+    } else {
+        int64_t nk = (int64_t)stv[kStKeys];
+        unsigned long long *cnt = nullptr;
+        GBT_TRY(dev_alloc(c, (size_t)(m + 1) * 8, (void **)&cnt));
+        std::vector<unsigned long long> h(m + 1, 0ull);
+        GBT_HIP(hipMemcpyAsync(cnt, h.data(), (m + 1) * 8, hipMemcpyHostToDevice, c->stream));
+        if (nk) {
+            k_feat_count<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, nk, cnt);
+            GBT_LAUNCHED();
+        }
+        GBT_HIP(hipMemcpyAsync(h.data(), cnt, m * 8, hipMemcpyDeviceToHost, c->stream));
+        GBT_HIP(hipStreamSynchronize(c->stream));
+        for (int32_t j = 0; j < m; ++j) seg[j + 1] = seg[j] + (int64_t)h[j];
+        feat_count.assign(h.begin(), h.begin() + m);
+        std::vector<unsigned long long> cur(m);
+        for (int32_t j = 0; j < m; ++j) cur[j] = (unsigned long long)seg[j];
+        GBT_HIP(hipMemcpyAsync(cnt, cur.data(), m * 8, hipMemcpyHostToDevice, c->stream));
+        sorted_bytes = (size_t)std::max<int64_t>(nk, 1) * 4;
+        gbt_status s = dev_alloc(c, sorted_bytes, (void **)&sorted);
+        if (s != GBT_OK) {
+            dev_free(c, cnt, (size_t)(m + 1) * 8);
+            return s;
+        }
+        if (nk) {
+            k_feat_scatter<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, q->keys, nk, cnt, sorted);
+            GBT_LAUNCHED();
+        }
+        GBT_HIP(hipStreamSynchronize(c->stream));
+        dev_free(c, cnt, (size_t)(m + 1) * 8);
+        keys = sorted;
+    }
+
+    // the order statistics of every feature (each rank's key, then the largest)
+    std::vector<uint32_t> vals;
+    std::vector<int64_t> N;
+    gbt_status status = select_cut_keys(c, keys, seg, B, &vals, &N);
+    if (status == GBT_E_BUDGET || status == GBT_E_OOM) status = bisect_cut_keys(c, keys, seg, B, &vals, &N);
+    dev_free(c, sorted, sorted_bytes);
+    GBT_TRY(status);
 
     // cuts: distinct candidates strictly below the maximum
     std::vector<int32_t> cut_ptr_h(m + 1, 0);
     std::vector<float> cut_values_h;
     for (int32_t j = 0; j < m; ++j) {
         if (N[j] > 0) {
-            GBT_CHECK(lo[j].back() == hi[j].back(), "cut search did not converge");
-            float top = key_float(lo[j].back());
-            for (size_t t = 0; t + 1 < rank[j].size(); ++t) {
-                float v = key_float(lo[j][t]);
-                if (v >= top) continue;
-                if (cut_values_h.size() > (size_t)cut_ptr_h[j] && v == cut_values_h.back()) continue;
-                cut_values_h.push_back(v);
+            const uint32_t *v = vals.data() + (size_t)j * B;
+            const uint32_t top = v[B - 1];
+            uint32_t last = 0;  // no key
+            for (int32_t k = 0; k + 1 < B; ++k) {
+                if (v[k] >= top || v[k] == last) continue;
+                last = v[k];
+                cut_values_h.push_back(key_float(last));
             }
         }
         cut_ptr_h[j + 1] = (int32_t)cut_values_h.size();

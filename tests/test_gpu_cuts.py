@@ -1,0 +1,83 @@
+"""The device selection of the quantile cuts at the edges of its branches
+(segments sorted whole by 256 or 1024 threads, split and gathered segments,
+buckets above one block's sort), bit for bit against the CPU oracle."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from tests.gpu_helpers import oracle_quantize, same_bits
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def gbt():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2005_09148_amd import gbt as g
+    return g
+
+
+def columns(n, seed):
+    """One column per distribution the selection can meet."""
+    r = np.random.default_rng(seed)
+    normal = r.normal(size=n)
+    zeros = np.where(r.random(n) < 0.7, 0.0, normal)  # one heavy value
+    huge = np.where(r.random(n) < 0.5, 1.0, -1.0) * 10.0 ** r.uniform(-44, 38, n)  # subnormals to near the largest
+    cols = [normal, r.random(n), r.integers(0, 5, n), zeros, np.full(n, -2.5), np.exp(4 * normal), huge,
+            np.arange(n) % 1000, 3e38 * np.where(np.arange(n) % 2, 1, -1), np.where(np.arange(n) % 97, np.nan, normal),
+            np.full(n, np.nan), np.where(r.random(n) < 0.999, 1e-3 * normal, 1e30 * normal)]
+    with np.errstate(over="ignore"):
+        X = np.stack(cols, 1).astype(np.float32)
+    X[np.isinf(X)] = np.float32(3e38)
+    X[r.random(n) < 0.01, 0] = np.float32(-0.0)
+    return X
+
+
+@pytest.mark.parametrize("n,max_bin", [(1, 256), (2, 2), (255, 16), (4096, 256), (4097, 256), (16384, 64),
+                                       (16385, 256), (16385, 2560), (65537, 3), (300_001, 256), (300_001, 2560)])
+def test_cuts_match_oracle(gbt, n, max_bin):
+    X = columns(n, n + max_bin)
+    cuts = orc.sketch_cuts_dense(X, max_bin)
+    ctx = gbt.Context(0)
+    mx = gbt.gbt_quantize(ctx, torch.from_numpy(X).cuda(), max_bin=max_bin)
+    cp, cv = mx.cuts()
+    assert same_bits(cp, cuts.cut_ptr) and same_bits(cv, cuts.cut_values)
+    ctx.close()
+
+
+def test_uneven_buckets(gbt):
+    """A run of close keys that the sample hardly meets: its bucket holds more
+    keys than one block sorts, and ranks fall into it."""
+    n = 4_000_000
+    x = torch.zeros(n, 1, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x[:, 0] = torch.randint(0, 30_000_000, (n,), generator=g, device="cuda").float()
+    ctx = gbt.Context(0)
+    mx = gbt.gbt_quantize(ctx, x, max_bin=1024)
+    v = np.sort(x.cpu().numpy()[:, 0])
+    c = np.unique(v[(np.arange(1, 1024) * n + 1023) // 1024 - 1])
+    assert same_bits(mx.cuts()[1], c[c < v[-1]])
+    ctx.close()
+
+
+@pytest.mark.parametrize("max_bin", [16, 256])
+def test_cuts_without_room_for_the_selection(gbt, max_bin):
+    """A budget that holds the keys but not the selection's workspace."""
+    n = 60_000
+    X = columns(n, 5)
+    m = X.shape[1]
+    cuts, _, _, page = oracle_quantize(X, max_bin)
+    ctx = gbt.Context(0, budget_bytes=n * m * 4 + 500_000)
+    q = gbt.Quantizer(ctx, m, n, max_bin=max_bin, page_home=gbt.HOME_PINNED_HOST)
+    q.sketch(torch.from_numpy(X).cuda())
+    q.finalize()
+    for lo in range(0, n, 7001):
+        q.encode(torch.from_numpy(X[lo:lo + 7001]).cuda())
+    mx = q.end()
+    cp, cv = mx.cuts()
+    assert same_bits(cp, cuts.cut_ptr) and same_bits(cv, cuts.cut_values)
+    assert same_bits(mx.pages(), page)
+    ctx.close()
