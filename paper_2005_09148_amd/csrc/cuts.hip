@@ -15,7 +15,7 @@
 //
 // Two passes over the keys instead of a bisection's nine, and no host work
 // between them but one read of the gathered size: 500 M keys (50 features x
-// 10 M rows, 256 bins) take 2.6 ms against 19.8 ms of bisection passes and
+// 10 M rows, 256 bins) take 2.3 ms against 19.8 ms of bisection passes and
 // 8 ms of host sorting between them.
 #include "cuts_impl.h"
 #include "wave_impl.h"
@@ -37,7 +37,7 @@ constexpr int kSample = kBigThreads * kItems;
 constexpr int kBuckets = 4096;
 constexpr int kCells = 4096;               // cells of the value-linear index over the split points
 constexpr int kCountThreads = 512;
-constexpr int kPickThreads = 512;          // sorts 8192 keys
+constexpr int kPickThreads = 256;          // sorts 1024 or 4096 keys
 constexpr int64_t kChunkMin = 1 << 16;     // keys per counting block, at least
 constexpr int kChunks = 1024;              // counting blocks, about (every block loads and stores 40 KB of tables)
 
@@ -51,28 +51,37 @@ __host__ __device__ inline int64_t cut_rank(int64_t k, int64_t N, int64_t B)
     return k < B ? (k * N + B - 1) / B - 1 : N - 1;
 }
 
-__device__ inline int pad_idx(int i) { return i + (i >> 4); }
-
-// Sorts kT * 16 keys, thread t's at positions 16 t .. 16 t + 15 of sk (padded
-// by one word per 16), in LDS: stable splits by two bits at a time, low to
-// high, with the four digit counts in the 16-bit fields of one 64-bit scan.
-// Digits in which no two keys of the block differ are skipped.
-template <int kT>
-__device__ inline void block_sort(uint32_t *sk, unsigned long long *wsum)
+// LDS place of key i when a thread owns kI keys: one word of padding per
+// thread, so that the threads' j-th keys lie in different banks.
+template <int kI = kItems>
+__device__ inline int pad_idx(int i)
 {
-    static_assert(kT * kItems <= 32768, "16-bit positions");
+    return i + i / kI;
+}
+
+// Sorts kT * kI keys, thread t's at positions kI t .. kI t + kI - 1 of sk
+// (padded by pad_idx<kI>), in LDS: stable splits by two bits at a time, low
+// to high, with the four digit counts in the 16-bit halves of two 32-bit
+// scans.  Digits in which no two keys of the block differ are skipped.  The
+// fields are 32 bits wide on purpose: a 64-bit vector shift whose amount sits
+// in the last register of a full allocation (here v79 of 80) shifted by
+// another wave's value as soon as a CU held two blocks.
+template <int kT, int kI = kItems>
+__device__ inline void block_sort(uint32_t *sk, uint2 *wsum)
+{
+    static_assert(kT * kI <= 32768, "16-bit positions");
     constexpr int kWaves = kT / 64;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, base = threadIdx.x * kItems;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, base = threadIdx.x * kI;
     __shared__ uint32_t s_or, s_and;
     if (threadIdx.x == 0) {
         s_or = 0u;
         s_and = 0xffffffffu;
     }
     __syncthreads();
-    uint32_t k[kItems], vo = 0u, va = 0xffffffffu;
+    uint32_t k[kI], vo = 0u, va = 0xffffffffu;
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        k[j] = sk[pad_idx(base + j)];
+    for (int j = 0; j < kI; ++j) {
+        k[j] = sk[pad_idx<kI>(base + j)];
         // padding and missing keys order last in any digit: every bit is set
         if (k[j] != kNanKey) {
             vo |= k[j];
@@ -91,30 +100,44 @@ __device__ inline void block_sort(uint32_t *sk, unsigned long long *wsum)
     const uint32_t vary = (s_or & ~s_and) | 0xff800000u;
     for (int sh = 0; sh < 32; sh += 2) {
         if (!((vary >> sh) & 3u)) continue;
-        unsigned long long c = 0;
+        // digits 0, 1 in the halves of lo, digits 2, 3 in those of hi
+        uint32_t lo = 0, hi = 0;
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) c += 1ull << (16 * ((k[j] >> sh) & 3u));
-        const unsigned long long x = wave_incl_sum(c);
-        if (lane == 63) wsum[wid] = x;
+        for (int j = 0; j < kI; ++j) {
+            const uint32_t d = (k[j] >> sh) & 3u, one = 1u << (16 * (d & 1u));
+            lo += d < 2u ? one : 0u;
+            hi += d < 2u ? 0u : one;
+        }
+        const uint32_t xl = wave_incl_sum(lo), xh = wave_incl_sum(hi);
+        if (lane == 63) wsum[wid] = make_uint2(xl, xh);
         __syncthreads();  // also: every thread has read its keys
-        unsigned long long off = x - c, tot = 0;
+        uint32_t tl = 0, th = 0;
+        lo = xl - lo;
+        hi = xh - hi;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            const unsigned long long v = wsum[w];
-            if (w < wid) off += v;
-            tot += v;
+            const uint2 v = wsum[w];
+            if (w < wid) {
+                lo += v.x;
+                hi += v.y;
+            }
+            tl += v.x;
+            th += v.y;
         }
         // digit d starts after all keys of lower digits
-        off += (tot << 16) + (tot << 32) + (tot << 48);
+        const uint32_t low = (tl & 0xffffu) + (tl >> 16);
+        lo += tl << 16;
+        hi += low * 0x10001u + (th << 16);
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) {
-            const int f = 16 * (int)((k[j] >> sh) & 3u);
-            sk[pad_idx((int)((off >> f) & 0xffffu))] = k[j];
-            off += 1ull << f;
+        for (int j = 0; j < kI; ++j) {
+            const uint32_t d = (k[j] >> sh) & 3u, f = 16 * (d & 1u);
+            sk[pad_idx<kI>((int)(((d < 2u ? lo : hi) >> f) & 0xffffu))] = k[j];
+            lo += d < 2u ? 1u << f : 0u;
+            hi += d < 2u ? 0u : 1u << f;
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) k[j] = sk[pad_idx(base + j)];
+        for (int j = 0; j < kI; ++j) k[j] = sk[pad_idx<kI>(base + j)];
     }
     __syncthreads();
 }
@@ -158,7 +181,7 @@ __global__ void __launch_bounds__(kT)
                 uint32_t *__restrict__ vals, int64_t *__restrict__ N_out)
 {
     __shared__ uint32_t sk[kT * kItems + kT];
-    __shared__ unsigned long long wsum[kT / 64];
+    __shared__ uint2 wsum[kT / 64];
     const CutSeg s = segs[blockIdx.x];
     for (int i = threadIdx.x; i < kT * kItems; i += kT) sk[pad_idx(i)] = i < s.len ? keys[s.begin + i] : kNanKey;
     __syncthreads();
@@ -206,7 +229,7 @@ __global__ void __launch_bounds__(kBigThreads)
     k_cut_split(const uint32_t *__restrict__ keys, const CutSeg *__restrict__ segs, CutTables *__restrict__ tables)
 {
     __shared__ uint32_t sk[kSample + kBigThreads];
-    __shared__ unsigned long long wsum[kBigThreads / 64];
+    __shared__ uint2 wsum[kBigThreads / 64];
     __shared__ int32_t isum[kBigThreads / 64];
     __shared__ int32_t s_wide;
     const CutSeg s = segs[blockIdx.x];
@@ -525,29 +548,43 @@ __global__ void __launch_bounds__(kCountThreads)
     }
 }
 
+// The ranks pk.r0 .. pk.r1 of a bucket of up to kPickThreads * kI keys.
+template <int kI>
+__device__ inline void pick_sorted(const uint32_t *a, const CutPick &pk, const uint32_t *__restrict__ rank_res,
+                                   uint32_t *__restrict__ vals, uint32_t *sk, uint2 *wsum)
+{
+    constexpr uint32_t kCap = kPickThreads * kI;
+    for (uint32_t i = threadIdx.x; i < kCap; i += kPickThreads) sk[pad_idx<kI>(i)] = i < pk.cnt ? a[i] : kNanKey;
+    __syncthreads();
+    block_sort<kPickThreads, kI>(sk, wsum);
+    for (int32_t r = pk.r0 + (int32_t)threadIdx.x; r <= pk.r1; r += kPickThreads)
+        vals[r] = sk[pad_idx<kI>((int)rank_res[r])];
+}
+
 // Block (i, s): the ranks of segment s's i-th gathered bucket.  A bucket of
-// up to 8192 keys is sorted in LDS; a larger one (an uneven sample) is
-// searched rank by rank, eight bits at a time.
+// up to 4096 keys is sorted in LDS (up to 1024 with a quarter of the keys
+// per thread: the passes' barriers, not their keys, set a block's time, and
+// buckets of 250 keys took 390 us per 7,000 in a 512-thread block of 16 keys
+// a thread); a larger one is searched rank by rank, eight bits at a time.
 __global__ void __launch_bounds__(kPickThreads)
     k_cut_pick(const uint32_t *__restrict__ gathered, const int64_t *__restrict__ base,
                const CutSeg *__restrict__ segs, const CutPick *__restrict__ picks, int32_t max_picks,
                const int64_t *__restrict__ gather_n, const uint32_t *__restrict__ rank_res, int32_t B,
                uint32_t *__restrict__ vals)
 {
-    constexpr int kCap = kPickThreads * kItems;
-    __shared__ uint32_t sk[kCap + kPickThreads];
-    __shared__ unsigned long long wsum[kPickThreads / 64];
+    __shared__ uint32_t sk[kPickThreads * kItems + kPickThreads];
+    __shared__ uint2 wsum[kPickThreads / 64];
     __shared__ uint32_t s_digit, s_below;
     if ((int64_t)blockIdx.x >= gather_n[2 * blockIdx.y + 1]) return;
     const CutPick pk = picks[(int64_t)blockIdx.y * max_picks + blockIdx.x];
     const uint32_t *a = gathered + base[blockIdx.y] + pk.off;
     const int64_t at = (int64_t)segs[blockIdx.y].feat * B;
-    if (pk.cnt <= (uint32_t)kCap) {
-        for (uint32_t i = threadIdx.x; i < (uint32_t)kCap; i += kPickThreads) sk[pad_idx(i)] = i < pk.cnt ? a[i] : kNanKey;
-        __syncthreads();
-        block_sort<kPickThreads>(sk, wsum);
-        for (int32_t r = pk.r0 + (int32_t)threadIdx.x; r <= pk.r1; r += kPickThreads)
-            vals[at + r] = sk[pad_idx((int)rank_res[at + r])];
+    if (pk.cnt <= kPickThreads * 4) {
+        pick_sorted<4>(a, pk, rank_res + at, vals + at, sk, wsum);
+        return;
+    }
+    if (pk.cnt <= kPickThreads * kItems) {
+        pick_sorted<kItems>(a, pk, rank_res + at, vals + at, sk, wsum);
         return;
     }
     for (int32_t r = pk.r0; r <= pk.r1; ++r) {
@@ -561,11 +598,16 @@ __global__ void __launch_bounds__(kPickThreads)
                 if ((k & mask) == prefix) atomicAdd(&sk[(k >> sh) & 255u], 1u);
             }
             __syncthreads();
-            if (threadIdx.x == 0) {
-                uint32_t d = 0, below = 0;
-                while (d < 255u && below + sk[d] <= want) below += sk[d++];
-                s_digit = d;
-                s_below = below;
+            if (threadIdx.x < 64) {  // the digit whose keys hold rank `want`: four digits per lane
+                const uint32_t *d4 = sk + 4 * threadIdx.x;
+                const uint32_t sum = d4[0] + d4[1] + d4[2] + d4[3], incl = wave_incl_sum(sum);
+                uint32_t below = incl - sum;
+                if (below <= want && want < incl) {
+                    uint32_t d = 0;
+                    while (below + d4[d] <= want) below += d4[d++];
+                    s_digit = 4 * threadIdx.x + d;
+                    s_below = below;
+                }
             }
             __syncthreads();
             prefix |= s_digit << sh;

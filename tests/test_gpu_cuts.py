@@ -4,7 +4,6 @@ buckets above one block's sort), bit for bit against the CPU oracle."""
 import numpy as np
 import pytest
 
-from oracle import oracle as orc
 from tests.gpu_helpers import oracle_quantize, same_bits
 
 pytestmark = pytest.mark.gpu
@@ -40,11 +39,36 @@ def columns(n, seed):
                                        (16385, 256), (16385, 2560), (65537, 3), (300_001, 256), (300_001, 2560)])
 def test_cuts_match_oracle(gbt, n, max_bin):
     X = columns(n, n + max_bin)
-    cuts = orc.sketch_cuts_dense(X, max_bin)
+    cuts, _, _, page = oracle_quantize(X, max_bin)
     ctx = gbt.Context(0)
     mx = gbt.gbt_quantize(ctx, torch.from_numpy(X).cuda(), max_bin=max_bin)
     cp, cv = mx.cuts()
     assert same_bits(cp, cuts.cut_ptr) and same_bits(cv, cuts.cut_values)
+    assert same_bits(mx.page(0), page)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,m,max_bin,ld,page_rows", [
+    (1, 1, 2, 1, 0), (255, 15, 256, 15, 0), (257, 17, 256, 19, 0), (511, 16, 300, 16, 200), (513, 33, 1100, 40, 0),
+    (1025, 31, 2560, 31, 512), (3000, 32, 2, 32, 0), (700, 100, 64, 101, 513), (2049, 47, 5, 48, 0)])
+def test_pages_match_oracle(gbt, n, m, max_bin, ld, page_rows):
+    """Edges of the encoder's tiles (rows, feature chunks, cuts per chunk),
+    a leading dimension above the columns, pages cut within a tile."""
+    r = np.random.default_rng(n + m)
+    X = r.normal(size=(n, ld)).astype(np.float32)
+    X[r.random(X.shape) < 0.1] = np.nan
+    X[:, 0] = np.floor(X[:, 0])
+    _, _, _, page = oracle_quantize(np.ascontiguousarray(X[:, :m]), max_bin)
+    ctx = gbt.Context(0)
+    Xd = torch.from_numpy(X).cuda()
+    q = gbt.Quantizer(ctx, m, n, max_bin=max_bin, page_rows=page_rows)
+    inp, _ = gbt.dense_input(Xd)
+    inp.n_cols = m
+    lib = gbt.lib()
+    gbt._check(lib.gbt_quantize_sketch_batch(q.h, gbt.C.byref(inp)))
+    q.finalize()
+    gbt._check(lib.gbt_quantize_encode_batch(q.h, gbt.C.byref(inp)))
+    assert same_bits(q.end().pages(), page)
     ctx.close()
 
 
