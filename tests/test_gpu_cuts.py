@@ -105,3 +105,30 @@ def test_cuts_without_room_for_the_selection(gbt, max_bin):
     assert same_bits(cp, cuts.cut_ptr) and same_bits(cv, cuts.cut_values)
     assert same_bits(mx.pages(), page)
     ctx.close()
+
+
+def test_kept_blocks(gbt):
+    """Large blocks that a context keeps and hands out again: the pages of
+    matrices alive meanwhile stay as a context with a budget (which keeps
+    none) makes them, and the bytes held are the same."""
+    plain = gbt.Context(0, budget_bytes=64 << 30)
+    ctx = gbt.Context(0)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    kept, want = [], []
+    for n in (2_500_000, 2_300_000, 3_000_000, 2_499_999):
+        X = torch.randn(n, 28, generator=g, device="cuda")
+        mx = gbt.gbt_quantize(ctx, X)
+        if n != 2_300_000:
+            kept.append(mx)
+            ref = gbt.gbt_quantize(plain, X)
+            want.append(ref.page(0))
+            assert same_bits(ref.cuts()[1], mx.cuts()[1])
+            ref.free()
+        else:
+            mx.free()
+    for mx, page in zip(kept, want):
+        assert same_bits(mx.page(0), page)
+        mx.free()
+    assert ctx.memory()[0] == plain.memory()[0]
+    ctx.close()
+    plain.close()
