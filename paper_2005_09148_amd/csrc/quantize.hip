@@ -17,6 +17,7 @@
 #include "cuts_impl.h"
 #include "hist_impl.h"
 #include "sketch_impl.h"
+#include "wave_impl.h"
 
 #include <algorithm>
 #include <cerrno>
@@ -115,39 +116,202 @@ __global__ void __launch_bounds__(kSkThreads)
 }
 
 // CSR batch: validate indices, count present (non-NaN) entries per row, and
-// append the (feature, key) pairs of sampled rows.
-__global__ void k_csr_sketch(const int64_t *__restrict__ indptr, const int32_t *__restrict__ idx,
-                             const float *__restrict__ val, int64_t rows, int32_t m, int64_t row0,
-                             int64_t stride, uint32_t *__restrict__ keys,
-                             int32_t *__restrict__ feats, unsigned long long *__restrict__ st)
+// append the (feature, key) pairs of sampled rows.  A block takes kCsrRows
+// rows and walks their entries, which are contiguous, with coalesced loads;
+// a bit per entry marks where rows start (only there may an index not
+// ascend), and the row of an entry is searched for only where it matters
+// (NaN values, skipped rows).  40 M entries of 2 M rows: 0.42 ms; one thread
+// per row, reading its 20 entries alone, took 2.5 ms.
+constexpr int kCsrRows = 256, kCsrTile = 8192;
+
+// Row whose entries [ptr[r], ptr[r + 1]) hold entry e (ptr[0] <= e < ptr[n]).
+__device__ inline int32_t row_of_entry(const int32_t *ptr, int32_t n, int32_t e)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= rows) return;
-    int64_t base = indptr[0];
-    int64_t e0 = indptr[i] - base, e1 = indptr[i + 1] - base;
-    int32_t prev = -1, cnt = 0;
-    bool inf = false, bad = e1 < e0;
-    for (int64_t e = e0; e < e1; ++e) {
-        int32_t j = idx[e];
-        float v = val[e];
-        if (j <= prev || j >= m) bad = true;
-        prev = j;
-        bool isn = v != v;
-        inf |= (!isn && (v - v) != 0.0f);
-        cnt += !isn;
+    int32_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (ptr[mid] <= e)
+            lo = mid;
+        else
+            hi = mid;
     }
-    if (bad) atomicOr(&st[kStBadIndex], 1ull);
+    return lo;
+}
+
+// The block's rows [r0, r0 + nr) as entry offsets from the first one's start
+// (*e0); false when they descend or leave [0, nnz].
+__device__ inline bool load_row_ptr(const int64_t *__restrict__ indptr, int64_t base, int64_t r0, int32_t nr,
+                                    int64_t nnz, int32_t *ptr, int64_t *e0, int32_t *s_bad)
+{
+    const int64_t first = indptr[r0] - base;
+    if (threadIdx.x == 0) *s_bad = 0;
+    __syncthreads();
+    bool bad = first < 0;
+    for (int32_t i = threadIdx.x; i <= nr; i += kCsrRows) {
+        const int64_t a = indptr[r0 + i] - base;
+        if (i > 0 && a < indptr[r0 + i - 1] - base) bad = true;
+        if (a > nnz || a - first > INT32_MAX) bad = true;
+        ptr[i] = (int32_t)(a - first);
+    }
+    if (bad) *s_bad = 1;
+    __syncthreads();
+    *e0 = first;
+    return *s_bad == 0;
+}
+
+__global__ void __launch_bounds__(kCsrRows)
+    k_csr_sketch(const int64_t *__restrict__ indptr, const int32_t *__restrict__ idx, const float *__restrict__ val,
+                 int64_t rows, int64_t nnz, int32_t m, int64_t row0, int64_t stride, uint32_t *__restrict__ keys,
+                 int32_t *__restrict__ feats, unsigned long long *__restrict__ st)
+{
+    __shared__ int32_t ptr[kCsrRows + 1], nan[kCsrRows];
+    __shared__ uint32_t start[kCsrTile / 32];
+    __shared__ int32_t wsum[kCsrRows / 64];
+    __shared__ int32_t s_bad, s_nan, s_max;
+    __shared__ unsigned long long s_at;
+    const int64_t r0 = (int64_t)blockIdx.x * kCsrRows;
+    const int32_t nr = (int32_t)(rows - r0 < kCsrRows ? rows - r0 : kCsrRows);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int64_t e0;
+    if (!load_row_ptr(indptr, indptr[0], r0, nr, nnz, ptr, &e0, &s_bad)) {
+        if (threadIdx.x == 0) atomicOr(&st[kStBadIndex], 1ull);
+        return;
+    }
+    nan[threadIdx.x] = 0;
+    if (threadIdx.x == 0) s_nan = s_max = 0;
+    const int32_t total = ptr[nr];
+    bool inf = false, bad = false;
+    for (int32_t t0 = 0; t0 < total; t0 += kCsrTile) {
+        static_assert(kCsrTile / 32 == kCsrRows, "one word of marks per thread");
+        start[threadIdx.x] = 0u;
+        __syncthreads();
+        if ((int32_t)threadIdx.x < nr) {
+            const int32_t s = ptr[threadIdx.x] - t0;
+            if (s >= 0 && s < kCsrTile) atomicOr(&start[s >> 5], 1u << (s & 31));
+        }
+        __syncthreads();
+        const int32_t n = min(kCsrTile, total - t0);
+#pragma unroll 4
+        for (int32_t i = threadIdx.x; i < n; i += kCsrRows) {
+            const int64_t e = e0 + t0 + i;
+            const int32_t j = idx[e];
+            const float v = val[e];
+            const int32_t prev = (start[i >> 5] >> (i & 31)) & 1u ? -1 : idx[e - 1];
+            if (j <= prev || j >= m) bad = true;
+            const bool isn = v != v;
+            inf |= !isn && (v - v) != 0.0f;
+            if (isn) {
+                atomicAdd(&nan[row_of_entry(ptr, nr, t0 + i)], 1);
+                s_nan = 1;
+            }
+        }
+        __syncthreads();
+    }
+    if (bad) s_bad = 1;
     if (inf) atomicOr(&st[kStInf], 1ull);
-    atomicMax(&st[kStMaxNnz], (unsigned long long)cnt);
-    if (bad || ((row0 + i) % stride) != 0 || cnt == 0) return;
-    unsigned long long at = atomicAdd(&st[kStKeys], (unsigned long long)cnt);
-    for (int64_t e = e0; e < e1; ++e) {
-        float v = val[e];
-        if (v != v) continue;
-        keys[at] = float_key(v);
-        feats[at] = idx[e];
-        ++at;
+    __syncthreads();
+    // the rows' present entries: the largest count, and the sampled rows' sum
+    int32_t cnt = 0, take = 0;
+    if ((int32_t)threadIdx.x < nr) {
+        cnt = ptr[threadIdx.x + 1] - ptr[threadIdx.x] - nan[threadIdx.x];
+        atomicMax(&s_max, cnt);
+        if (!s_bad && (row0 + r0 + threadIdx.x) % stride == 0) take = cnt;
     }
+    take = wave_total(take);
+    if (lane == 0) wsum[wid] = take;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (s_bad) atomicOr(&st[kStBadIndex], 1ull);
+        if ((unsigned long long)s_max > __hip_atomic_load(&st[kStMaxNnz], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&st[kStMaxNnz], (unsigned long long)s_max);
+        int64_t sum = 0;
+        for (int w = 0; w < kCsrRows / 64; ++w) sum += wsum[w];
+        s_at = sum ? atomicAdd(&st[kStKeys], (unsigned long long)sum) : 0ull;
+    }
+    __syncthreads();
+    if (s_bad) return;
+    unsigned long long at = s_at;
+    if (stride == 1 && !s_nan) {
+#pragma unroll 4
+        for (int32_t i = threadIdx.x; i < total; i += kCsrRows) {
+            keys[at + i] = float_key(val[e0 + i]);
+            feats[at + i] = idx[e0 + i];
+        }
+        return;
+    }
+    for (int32_t t0 = 0; t0 < total; t0 += kCsrRows) {
+        const int32_t i = t0 + (int32_t)threadIdx.x;
+        bool keep = false;
+        float v = 0.0f;
+        if (i < total) {
+            v = val[e0 + i];
+            keep = v == v && (stride == 1 || (row0 + r0 + row_of_entry(ptr, nr, i)) % stride == 0);
+        }
+        const unsigned long long mask = __ballot(keep);
+        __syncthreads();  // the counts of the step before are read
+        if (lane == 0) wsum[wid] = __popcll(mask);
+        __syncthreads();
+        unsigned long long o = at + __popcll(mask & ((1ull << lane) - 1ull));
+        for (int w = 0; w < kCsrRows / 64; ++w) {
+            if (w < wid) o += wsum[w];
+            at += wsum[w];
+        }
+        if (keep) {
+            keys[o] = float_key(v);
+            feats[o] = idx[e0 + i];
+        }
+    }
+}
+
+// Grouping pairs by feature: blocks of kGroupThreads over equal ranges of the
+// pairs count them per feature in LDS (cnt[block][feature]); the counts
+// become each block's first place in every feature's segment, and the
+// blocks scatter their keys with LDS cursors.  Two global atomics per pair,
+// which the few popular features serialized, took 83 ms for 40 M pairs of
+// 2000 features; this form 0.62 ms.  Features above kGroupFeats (their counters fill the LDS)
+// take the global counters below.
+constexpr int kGroupThreads = 1024, kGroupBlocks = 512, kGroupFeats = 16384;
+
+__global__ void __launch_bounds__(kGroupThreads)
+    k_group_count(const int32_t *__restrict__ feats, int64_t n, int64_t per, int32_t m, uint32_t *__restrict__ cnt)
+{
+    extern __shared__ uint32_t group_lds[];
+    for (int32_t j = threadIdx.x; j < m; j += kGroupThreads) group_lds[j] = 0u;
+    __syncthreads();
+    const int64_t b = (int64_t)blockIdx.x * per, e = min(n, b + per);
+#pragma unroll 4
+    for (int64_t i = b + threadIdx.x; i < e; i += kGroupThreads) atomicAdd(&group_lds[feats[i]], 1u);
+    __syncthreads();
+    for (int32_t j = threadIdx.x; j < m; j += kGroupThreads) cnt[(int64_t)blockIdx.x * m + j] = group_lds[j];
+}
+
+__global__ void k_group_offsets(uint32_t *__restrict__ cnt, int32_t blocks, int32_t m,
+                                unsigned long long *__restrict__ total)
+{
+    const int32_t j = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (j >= m) return;
+    uint32_t run = 0;
+#pragma unroll 8
+    for (int32_t b = 0; b < blocks; ++b) {
+        const uint32_t c = cnt[(int64_t)b * m + j];
+        cnt[(int64_t)b * m + j] = run;
+        run += c;
+    }
+    total[j] = run;
+}
+
+__global__ void __launch_bounds__(kGroupThreads)
+    k_group_scatter(const int32_t *__restrict__ feats, const uint32_t *__restrict__ keys, int64_t n, int64_t per,
+                    int32_t m, const uint32_t *__restrict__ cnt, const unsigned long long *__restrict__ base,
+                    uint32_t *__restrict__ out)
+{
+    extern __shared__ uint32_t group_lds[];
+    for (int32_t j = threadIdx.x; j < m; j += kGroupThreads)
+        group_lds[j] = (uint32_t)base[j] + cnt[(int64_t)blockIdx.x * m + j];
+    __syncthreads();
+    const int64_t b = (int64_t)blockIdx.x * per, e = min(n, b + per);
+#pragma unroll 4
+    for (int64_t i = b + threadIdx.x; i < e; i += kGroupThreads) out[atomicAdd(&group_lds[feats[i]], 1u)] = keys[i];
 }
 
 __global__ void k_feat_count(const int32_t *__restrict__ feats, int64_t n,
@@ -232,28 +396,6 @@ __device__ inline int32_t lookup_bin(const float *__restrict__ cuts, int32_t nc,
     }
     return lo;
 }
-
-struct BitWriter {
-    uint32_t *out;
-    uint64_t acc = 0;
-    int32_t nbits = 0, k = 0;
-    __device__ BitWriter(uint32_t *o) : out(o) {}
-    __device__ void put(uint32_t sym, int32_t w)
-    {
-        acc |= (uint64_t)sym << nbits;
-        nbits += w;
-        while (nbits >= 32) {
-            out[k++] = (uint32_t)acc;
-            acc >>= 32;
-            nbits -= 32;
-        }
-    }
-    __device__ void finish(int32_t row_words)
-    {
-        if (nbits > 0) out[k++] = (uint32_t)acc;
-        while (k < row_words) out[k++] = 0u;
-    }
-};
 
 // Dense rows: a block encodes kEncRows rows, kEncCols features (fewer when
 // their cuts are many) at a time: their cuts, each feature's padded to
@@ -358,35 +500,90 @@ __global__ void __launch_bounds__(kEncRows)
     while (k < row_words) emit(0u);
 }
 
-__global__ void k_encode_csr(const int64_t *__restrict__ indptr, const int32_t *__restrict__ idx,
-                             const float *__restrict__ val, int64_t rows, const int64_t *__restrict__ entry0,
-                             const int32_t *__restrict__ cut_ptr,
-                             const float *__restrict__ cut_values,
-                             const int32_t *__restrict__ bin_ptr, int32_t w, int32_t stride,
-                             int32_t row_words, uint32_t null_sym, uint32_t *__restrict__ out,
-                             unsigned long long *__restrict__ st)
+// CSR rows: a block finds the symbols of kCsrRows rows entry by entry (the
+// entries are contiguous: coalesced loads, and a thread's searches of the
+// cuts overlap) into LDS; then a lane owns a row and packs its symbols, four
+// words per store.  Rows that fill more than the LDS tile together are
+// searched by their own lane.  2 M rows of 20 entries: 0.76 ms against 1.36
+// ms with a lane per row throughout.
+__global__ void __launch_bounds__(kCsrRows)
+    k_encode_csr(const int64_t *__restrict__ indptr, const int32_t *__restrict__ idx, const float *__restrict__ val,
+                 int64_t rows, int64_t nnz, int32_t m, const int64_t *__restrict__ entry0,
+                 const int32_t *__restrict__ cut_ptr, const float *__restrict__ cut_values,
+                 const int32_t *__restrict__ bin_ptr, int32_t w, int32_t stride, int32_t row_words, uint32_t null_sym,
+                 uint32_t *__restrict__ out, unsigned long long *__restrict__ st)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= rows) return;
-    int64_t base = entry0[0];
-    int64_t e0 = indptr[i] - base, e1 = indptr[i + 1] - base;
-    BitWriter bw(out + i * row_words);
-    int32_t s = 0;
-    for (int64_t e = e0; e < e1; ++e) {
-        float v = val[e];
-        if (v != v) continue;
-        if (s >= stride) {  // more entries than the sketch pass saw in any row
-            atomicOr(&st[kStBadIndex], 1ull);
-            break;
-        }
-        int32_t j = idx[e];
-        int32_t c0 = cut_ptr[j];
-        bw.put((uint32_t)bin_ptr[j] + (uint32_t)lookup_bin(cut_values + c0, cut_ptr[j + 1] - c0, v),
-               w);
-        ++s;
+    __shared__ int32_t ptr[kCsrRows + 1];
+    __shared__ uint32_t sym[kCsrTile];
+    __shared__ int32_t s_bad;
+    constexpr uint32_t kSkip = 0xffffffffu;  // a missing value
+    const int64_t r0 = (int64_t)blockIdx.x * kCsrRows;
+    const int32_t nr = (int32_t)(rows - r0 < kCsrRows ? rows - r0 : kCsrRows);
+    int64_t e0;
+    if (!load_row_ptr(indptr, entry0[0], r0, nr, nnz, ptr, &e0, &s_bad)) {
+        if (threadIdx.x == 0) atomicOr(&st[kStBadIndex], 1ull);
+        return;
     }
-    for (; s < stride; ++s) bw.put(null_sym, w);
-    bw.finish(row_words);
+    const int32_t total = ptr[nr];
+    auto symbol = [&](int64_t e) -> uint32_t {
+        const float v = val[e];
+        const int32_t j = idx[e];
+        if (v != v) return kSkip;
+        if (j < 0 || j >= m) {  // not the batch that was sketched
+            s_bad = 1;
+            return kSkip;
+        }
+        const int32_t c0 = cut_ptr[j];
+        return (uint32_t)bin_ptr[j] + (uint32_t)lookup_bin(cut_values + c0, cut_ptr[j + 1] - c0, v);
+    };
+    const bool staged = total <= kCsrTile;
+    if (staged) {
+#pragma unroll 4
+        for (int32_t i = threadIdx.x; i < total; i += kCsrRows) sym[i] = symbol(e0 + i);
+        __syncthreads();
+    }
+    const int32_t row = (int32_t)threadIdx.x;
+    if (row < nr) {
+        int32_t e = ptr[row];
+        const int32_t e1 = ptr[row + 1];
+        uint4 *dst = (uint4 *)(out + (r0 + row) * row_words);
+        uint4 q = make_uint4(0u, 0u, 0u, 0u);
+        uint64_t acc = 0;
+        int32_t nbits = 0, k = 0;  // the same in every lane
+        auto emit = [&](uint32_t v) {
+            if ((k & 3) == 0) q.x = v;
+            if ((k & 3) == 1) q.y = v;
+            if ((k & 3) == 2) q.z = v;
+            if ((k & 3) == 3) {
+                q.w = v;
+                dst[k >> 2] = q;
+            }
+            ++k;
+        };
+        auto next = [&]() -> uint32_t {
+            while (e < e1) {
+                const uint32_t s = staged ? sym[e] : symbol(e0 + e);
+                ++e;
+                if (s != kSkip) return s;
+            }
+            return kSkip;
+        };
+        for (int32_t s = 0; s < stride; ++s) {
+            const uint32_t v = next();
+            acc |= (uint64_t)(v == kSkip ? null_sym : v) << nbits;
+            nbits += w;
+            if (nbits >= 32) {
+                emit((uint32_t)acc);
+                acc >>= 32;
+                nbits -= 32;
+            }
+        }
+        if (nbits > 0) emit((uint32_t)acc);
+        while (k < row_words) emit(0u);
+        if (next() != kSkip) s_bad = 1;  // more entries than the sketch pass saw in any row
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_bad) atomicOr(&st[kStBadIndex], 1ull);
 }
 
 unsigned grid_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
@@ -530,45 +727,81 @@ void free_quantizer(gbt_quantizer *q)
     delete q;
 }
 
-// A merged sketch's CSR batch: the batch's (feature, key) pairs grouped by
-// feature (counts, then a scatter), summarised and merged.
-gbt_status csr_merge_batch(gbt_quantizer *q)
+// The quantizer's nk (feature, key) pairs grouped by feature: feature j's keys
+// at [seg[j], seg[j + 1]) of the buffer `room` gives for nk keys.
+template <typename Room>
+gbt_status group_by_feature(gbt_quantizer *q, int64_t nk, std::vector<int64_t> *seg, Room &&room)
 {
     gbt_ctx *c = q->ctx;
     const int32_t m = q->m;
+    seg->assign(m + 1, 0);
+    const bool lds = m <= kGroupFeats && nk < ((int64_t)1 << 32);
+    // enough pairs per block to pay for its pass over the features
+    const int64_t per = std::max<int64_t>((nk + kGroupBlocks - 1) / kGroupBlocks, std::max(kGroupThreads * 4, m));
+    const int64_t blocks = (nk + per - 1) / per;
+    const size_t o_cnt = ((size_t)m * 8 + 255) / 256 * 256, bytes = o_cnt + (lds ? (size_t)blocks * m * 4 : 0);
+    char *w = nullptr;
+    GBT_TRY(dev_alloc(c, bytes, (void **)&w));
+    auto run = [&]() -> gbt_status {
+        unsigned long long *tot = (unsigned long long *)w;
+        uint32_t *cnt = (uint32_t *)(w + o_cnt);
+        std::vector<unsigned long long> h(m, 0ull);
+        const size_t lds_bytes = (size_t)m * 4;
+        if (nk && lds) {
+            k_group_count<<<(unsigned)blocks, kGroupThreads, lds_bytes, c->stream>>>(q->feats, nk, per, m, cnt);
+            GBT_LAUNCHED();
+            k_group_offsets<<<grid_for(m, 64), 64, 0, c->stream>>>(cnt, (int32_t)blocks, m, tot);
+            GBT_LAUNCHED();
+        } else {
+            GBT_HIP(hipMemcpyAsync(tot, h.data(), (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
+            if (nk) {
+                k_feat_count<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, nk, tot);
+                GBT_LAUNCHED();
+            }
+        }
+        GBT_HIP(hipMemcpyAsync(h.data(), tot, (size_t)m * 8, hipMemcpyDeviceToHost, c->stream));
+        GBT_HIP(hipStreamSynchronize(c->stream));
+        for (int32_t j = 0; j < m; ++j) {
+            (*seg)[j + 1] = (*seg)[j] + (int64_t)h[j];
+            h[j] = (unsigned long long)(*seg)[j];
+        }
+        uint32_t *out = nullptr;
+        GBT_TRY(room(nk, &out));
+        if (nk == 0) return GBT_OK;
+        GBT_HIP(hipMemcpyAsync(tot, h.data(), (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
+        if (lds)
+            k_group_scatter<<<(unsigned)blocks, kGroupThreads, lds_bytes, c->stream>>>(q->feats, q->keys, nk, per, m,
+                                                                                       cnt, tot, out);
+        else
+            k_feat_scatter<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, q->keys, nk, tot, out);
+        GBT_LAUNCHED();
+        return GBT_OK;
+    };
+    const gbt_status s = run();
+    (void)hipStreamSynchronize(c->stream);
+    dev_free(c, w, bytes);
+    return s;
+}
+
+// A merged sketch's CSR batch: the batch's (feature, key) pairs grouped by
+// feature, summarised and merged.
+gbt_status csr_merge_batch(gbt_quantizer *q)
+{
+    gbt_ctx *c = q->ctx;
     unsigned long long stv[kStWords];
     GBT_TRY(read_status(q, stv));
     GBT_CHECK(!stv[kStBadIndex], "CSR column indices must be in [0, n_cols) and strictly ascending");
     const int64_t nk = (int64_t)stv[kStKeys];
     if (nk == 0) return GBT_OK;
-    unsigned long long *cnt = nullptr;
-    GBT_TRY(dev_alloc(c, (size_t)(m + 1) * 8, (void **)&cnt));
-    std::vector<unsigned long long> h(m + 1, 0ull), cur(m);
-    gbt_status s = GBT_OK;
-    auto run = [&]() -> gbt_status {
-        GBT_HIP(hipMemcpyAsync(cnt, h.data(), (m + 1) * 8, hipMemcpyHostToDevice, c->stream));
-        k_feat_count<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, nk, cnt);
-        GBT_LAUNCHED();
-        GBT_HIP(hipMemcpyAsync(h.data(), cnt, m * 8, hipMemcpyDeviceToHost, c->stream));
-        GBT_HIP(hipStreamSynchronize(c->stream));
-        std::vector<int64_t> sb(m), sl(m);
-        int64_t o = 0;
-        for (int32_t j = 0; j < m; ++j) {
-            sb[j] = o;
-            sl[j] = (int64_t)h[j];
-            cur[j] = (unsigned long long)o;
-            o += (int64_t)h[j];
-        }
-        GBT_TRY(ensure_buf(c, (void **)&q->bkeys, &q->bkeys_bytes, (size_t)nk * 4));
-        GBT_HIP(hipMemcpyAsync(cnt, cur.data(), m * 8, hipMemcpyHostToDevice, c->stream));
-        k_feat_scatter<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, q->keys, nk, cnt, q->bkeys);
-        GBT_LAUNCHED();
-        return merge_sketch_add(c, q->ms, q->bkeys, sb.data(), sl.data());
-    };
-    s = run();
-    (void)hipStreamSynchronize(c->stream);
-    dev_free(c, cnt, (size_t)(m + 1) * 8);
-    return s;
+    std::vector<int64_t> seg;
+    GBT_TRY(group_by_feature(q, nk, &seg, [&](int64_t n, uint32_t **out) -> gbt_status {
+        GBT_TRY(ensure_buf(c, (void **)&q->bkeys, &q->bkeys_bytes, (size_t)n * 4));
+        *out = q->bkeys;
+        return GBT_OK;
+    }));
+    std::vector<int64_t> len(q->m);
+    for (int32_t j = 0; j < q->m; ++j) len[j] = seg[j + 1] - seg[j];
+    return merge_sketch_add(c, q->ms, q->bkeys, seg.data(), len.data());
 }
 
 }  // namespace
@@ -698,8 +931,8 @@ gbt_status gbt_quantize_sketch_batch(gbt_quantizer *q, const gbt_input *batch)
                 q->keys_bytes = q->feats_bytes = (size_t)cap * 4;
                 q->keys_cap = cap;
             }
-            k_csr_sketch<<<grid_for(b.rows, 256), 256, 0, c->stream>>>(
-                b.indptr, b.indices, b.values, b.rows, q->m, q->sketched_rows, q->stride, q->keys,
+            k_csr_sketch<<<grid_for(b.rows, kCsrRows), kCsrRows, 0, c->stream>>>(
+                b.indptr, b.indices, b.values, b.rows, b.nnz, q->m, q->sketched_rows, q->stride, q->keys,
                 q->feats, q->st);
             GBT_LAUNCHED();
             if (q->ms) GBT_TRY(csr_merge_batch(q));
@@ -950,34 +1183,17 @@ gbt_status gbt_quantize_finalize_cuts(gbt_quantizer *q)
     if (q->kind == GBT_INPUT_DENSE_F32) {
         for (int32_t j = 0; j <= m; ++j) seg[j] = (int64_t)j * q->n_sketch;
     } else {
-        int64_t nk = (int64_t)stv[kStKeys];
-        unsigned long long *cnt = nullptr;
-        GBT_TRY(dev_alloc(c, (size_t)(m + 1) * 8, (void **)&cnt));
-        std::vector<unsigned long long> h(m + 1, 0ull);
-        GBT_HIP(hipMemcpyAsync(cnt, h.data(), (m + 1) * 8, hipMemcpyHostToDevice, c->stream));
-        if (nk) {
-            k_feat_count<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, nk, cnt);
-            GBT_LAUNCHED();
-        }
-        GBT_HIP(hipMemcpyAsync(h.data(), cnt, m * 8, hipMemcpyDeviceToHost, c->stream));
-        GBT_HIP(hipStreamSynchronize(c->stream));
-        for (int32_t j = 0; j < m; ++j) seg[j + 1] = seg[j] + (int64_t)h[j];
-        feat_count.assign(h.begin(), h.begin() + m);
-        std::vector<unsigned long long> cur(m);
-        for (int32_t j = 0; j < m; ++j) cur[j] = (unsigned long long)seg[j];
-        GBT_HIP(hipMemcpyAsync(cnt, cur.data(), m * 8, hipMemcpyHostToDevice, c->stream));
-        sorted_bytes = (size_t)std::max<int64_t>(nk, 1) * 4;
-        gbt_status s = dev_alloc(c, sorted_bytes, (void **)&sorted);
+        gbt_status s = group_by_feature(q, (int64_t)stv[kStKeys], &seg, [&](int64_t n, uint32_t **out) -> gbt_status {
+            sorted_bytes = (size_t)std::max<int64_t>(n, 1) * 4;
+            GBT_TRY(dev_alloc(c, sorted_bytes, (void **)&sorted));
+            *out = sorted;
+            return GBT_OK;
+        });
         if (s != GBT_OK) {
-            dev_free(c, cnt, (size_t)(m + 1) * 8);
+            dev_free(c, sorted, sorted_bytes);
             return s;
         }
-        if (nk) {
-            k_feat_scatter<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, q->keys, nk, cnt, sorted);
-            GBT_LAUNCHED();
-        }
-        GBT_HIP(hipStreamSynchronize(c->stream));
-        dev_free(c, cnt, (size_t)(m + 1) * 8);
+        for (int32_t j = 0; j < m; ++j) feat_count.push_back(seg[j + 1] - seg[j]);
         keys = sorted;
     }
 
@@ -1101,8 +1317,8 @@ gbt_status gbt_quantize_encode_batch(gbt_quantizer *q, const gbt_input *batch)
                 b.values + r * b.ld, n, mx->m, b.ld, mx->cut_ptr_d, mx->cut_values_d, mx->w, mx->row_words,
                 mx->null_sym, lg, cols, out);
         else
-            k_encode_csr<<<grid_for(n, 256), 256, 0, c->stream>>>(
-                b.indptr + r, b.indices, b.values, n, b.indptr, mx->cut_ptr_d, mx->cut_values_d, mx->bin_ptr_d, mx->w,
+            k_encode_csr<<<grid_for(n, kCsrRows), kCsrRows, 0, c->stream>>>(
+                b.indptr + r, b.indices, b.values, n, b.nnz, mx->m, b.indptr, mx->cut_ptr_d, mx->cut_values_d, mx->bin_ptr_d, mx->w,
                 mx->stride, mx->row_words, mx->null_sym, out, q->st);
         GBT_LAUNCHED();
         return GBT_OK;

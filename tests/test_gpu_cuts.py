@@ -132,3 +132,56 @@ def test_kept_blocks(gbt):
     assert ctx.memory()[0] == plain.memory()[0]
     ctx.close()
     plain.close()
+
+
+def csr_rows(n, m, density, seed, nan=0.0, empty=0.0):
+    r = np.random.default_rng(seed)
+    lens = np.minimum(r.binomial(m, density, n), m)
+    lens[r.random(n) < empty] = 0
+    cols = [np.sort(r.choice(m, k, replace=False)) for k in lens]
+    indptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    idx = np.concatenate(cols + [np.zeros(0, np.int64)]).astype(np.int32)
+    val = np.exp(r.normal(size=len(idx))).astype(np.float32)
+    val[r.random(len(val)) < nan] = np.nan
+    return {"kind": "csr", "indptr": indptr, "indices": idx, "values": val, "m": m}
+
+
+@pytest.mark.parametrize("n,m,density,nan,empty,max_rows,device", [
+    (1, 3, 1.0, 0.0, 0.0, 0, True), (255, 20, 0.3, 0.1, 0.3, 0, True), (513, 7, 0.9, 0.5, 0.1, 0, False),
+    (700, 2000, 0.6, 0.02, 0.05, 0, True), (300, 40, 0.0, 0.0, 0.0, 0, True), (5003, 30, 0.2, 0.1, 0.2, 1000, True),
+    (400, 20_000, 0.003, 0.1, 0.1, 0, True), (60_001, 12, 0.7, 0.0, 0.0, 0, True)])
+def test_csr_matches_oracle(gbt, n, m, density, nan, empty, max_rows, device):
+    """Edges of the CSR kernels: ragged and empty rows, missing values stored,
+    rows past the LDS tile, skipped sketch rows, more features than the
+    grouping's LDS counters."""
+    d = csr_rows(n, m, density, n + m, nan, empty)
+    cuts, _, _, page = oracle_quantize(d, 16, max_rows or 1 << 24)
+    ctx = gbt.Context(0)
+    dd = dict(d, **{k: torch.from_numpy(d[k]).cuda() for k in ("indptr", "indices", "values")}) if device else d
+    mx = gbt.gbt_quantize(ctx, dd, max_bin=16, sketch_max_rows=max_rows)
+    cp, cv = mx.cuts()
+    assert same_bits(cp, cuts.cut_ptr) and same_bits(cv, cuts.cut_values)
+    assert same_bits(mx.page(0), page)
+    ctx.close()
+
+
+@pytest.mark.parametrize("what", ["equal", "descending", "negative", "large", "indptr"])
+def test_csr_refuses_bad_indices(gbt, what):
+    d = csr_rows(600, 30, 0.4, 1)
+    row = int(np.flatnonzero(np.diff(d["indptr"]) >= 3)[-1])
+    e = int(d["indptr"][row])
+    if what == "equal":
+        d["indices"][e + 1] = d["indices"][e]
+    elif what == "descending":
+        d["indices"][e:e + 2] = d["indices"][e:e + 2][::-1]
+    elif what == "negative":
+        d["indices"][e] = -1
+    elif what == "large":
+        d["indices"][int(d["indptr"][row + 1]) - 1] = 30
+    else:
+        d["indptr"][row] = d["indptr"][row + 1] + 1
+    ctx = gbt.Context(0)
+    with pytest.raises(gbt.GbtError) as err:
+        gbt.gbt_quantize(ctx, d, max_bin=16)
+    assert err.value.code == gbt.GBT_E_INVALID
+    ctx.close()
