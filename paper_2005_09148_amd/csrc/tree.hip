@@ -13,6 +13,7 @@
 #include "hist_impl.h"
 #include "split_impl.h"
 #include "plan_impl.h"
+#include "predict_impl.h"
 
 namespace gbt {
 
@@ -1943,13 +1944,26 @@ gbt_status gbt_predict(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, const
     GBT_TRY(set_device(c));
     gbt_node *nodes_d = nullptr;
     int64_t *offs_d = nullptr;
-    if (n_trees) GBT_TRY(upload_trees(c, trees, n_trees, &nodes_d, &offs_d));
+    // dense rows and trees that fit the LDS are walked there; others (CSR
+    // rows, deep trees, very wide rows) in global memory
+    const bool dense = binned ? !binned->sparse : raw->kind == GBT_INPUT_DENSE_F32 && raw->n_cols > 0;
+    const int32_t block_rows = dense ? lds_predict_rows(trees, n_trees, binned ? binned->n_rows : raw->n_rows,
+                                                        binned ? binned->row_words : raw->n_cols)
+                                     : 0;
+    LdsTrees lt;
+    bool in_lds = block_rows > 0;
+    if (in_lds)
+        GBT_TRY(lds_upload_trees(c, trees, n_trees, binned ? binned->w : 0, binned ? binned->m : raw->n_cols, &lt,
+                                 &in_lds));
+    if (n_trees && !in_lds) GBT_TRY(upload_trees(c, trees, n_trees, &nodes_d, &offs_d));
     if (binned) {
         GBT_CHECK(binned->n_rows == 0 || margin_out_d, "output is NULL");
         Geo geo = geo_of(binned);
         GBT_TRY(for_each_chunk(
             c, binned,
             [&](const uint32_t *words, int64_t row0, int64_t rows) -> gbt_status {
+                if (in_lds)
+                    return lds_predict_binned(c, lt, words, rows, geo, base_margin, block_rows, margin_out_d + row0);
                 if (geo.row_words <= kWalkMaxWords)
                     k_predict_binned<true><<<blocks(rows), kWalkThreads, walk_lds_bytes(geo), c->stream>>>(
                         words, rows, geo, nodes_d, offs_d, n_trees, base_margin, margin_out_d + row0);
@@ -1967,7 +1981,11 @@ gbt_status gbt_predict(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, const
             GBT_CHECK(margin_out_d, "output is NULL");
             if (raw->kind == GBT_INPUT_DENSE_F32) {
                 GBT_CHECK(raw->values && raw->ld >= raw->n_cols, "bad dense input");
-                k_predict_raw_dense<<<blocks(raw->n_rows), 256, 0, c->stream>>>(
+                if (in_lds)
+                    GBT_TRY(lds_predict_raw(c, lt, raw->values, raw->n_rows, raw->n_cols, raw->ld, base_margin,
+                                            block_rows, margin_out_d));
+                else
+                    k_predict_raw_dense<<<blocks(raw->n_rows), 256, 0, c->stream>>>(
                     raw->values, raw->n_rows, raw->ld, nodes_d, offs_d, n_trees, base_margin, margin_out_d);
             } else {
                 GBT_CHECK(raw->indptr && (raw->nnz == 0 || (raw->indices && raw->values)), "bad CSR input");
