@@ -150,6 +150,11 @@ gbt_status lambda_sums(gbt_ctx *c, int32_t loss, const float *margin, const floa
 // fx_max_done: the maxima of |g'| and |h'| are already in st (fused upstream)
 gbt_status fixed_point(gbt_ctx *c, const double *gw, int64_t R, SampleState *st, int64_t *q,
                        bool fx_max_done = false);
+// The fixed-point pairs of all n rows with weight 1, their exponents and sums
+// (into st), recomputed from margins and labels: what launch_gradients,
+// gw_all and fixed_point give, with nothing else kept per row.
+gbt_status fixed_point_rows(gbt_ctx *c, int32_t loss, const float *margin, const float *label, int64_t n,
+                            SampleState *st, int64_t *q);
 // Gradients of all rows and, fused, the maximum of r^2 = g^2 + lambda h^2;
 // with e_spec (not kNoKeySpec) also the MVS keys' maximum and sum with that
 // key exponent, st->e_key = e_spec (to be checked by mvs_threshold); with

@@ -243,11 +243,15 @@ gbt_status sample_run(gbt_ctx *c, const gbt_matrix *mx, const float *gpair, cons
     const int kind = gpair ? kSrcGpair : kSrcMargin;
     bool fx_max_done = false;
 
-    if (sp.f >= 1.0 && all_device_single(mx) && gpair) {
+    if (sp.f >= 1.0 && all_device_single(mx) && (gpair || !read_state)) {
         // no sampling: the data page trains as it is
         o->alias = true;
         o->page = mx->pages[0].words;
         o->R = n;
+        if (!gpair) {  // the tree driver reads nothing but the fixed-point pairs
+            GBT_TRY(bufs.get(kScrQ, (size_t)std::max<int64_t>(n, 1) * 16, (void **)&o->q));
+            return fixed_point_rows(c, sp.loss, margin, label, n, st, o->q);
+        }
         GBT_TRY(bufs.get(kScrGw, (size_t)std::max<int64_t>(n, 1) * 16, (void **)&o->gw));
         GBT_TRY(gw_all(c, gpair, n, o->gw));
     } else {
@@ -913,11 +917,12 @@ struct TreePending {
 
 // Queues one tree: gradients to the margin update, and the tree's copy into
 // the pinned result res_h (res_d on the device), then `done` when not NULL.
-// spec_prev: the MVS key exponent is guessed from the sampling state's last
-// tree on the device (that tree is queued, and the host has not read it).
-// reset_state: the tree's last kernel resets the sampling state for a next
-// tree, which is then queued with state_ready (it skips state_init; both
-// only for sampled trees on device pages).
+// spec_prev: an earlier tree of the same call is queued (the host may not have
+// read it): the MVS key exponent is guessed from the sampling state's last
+// tree on the device, and a training page that is the matrix's own keeps that
+// tree's slot table.  reset_state: the tree's last kernel resets the
+// sampling state for a next tree, which is then queued with state_ready (it
+// skips state_init; both only for trees on device pages).
 static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const float *label, float *margin,
                                      const gbt_train_params *p, bool want_stats, void *res_h, void *res_d,
                                      hipEvent_t done, bool spec_prev, bool state_ready, bool reset_state,
@@ -946,7 +951,11 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
     if (mvs && !spec_prev && c->key_n_last == n && c->key_lambda_last == sample_lambda(sp)) e_spec = c->key_e_last;
     c->key_n_last = -1;  // set again when this tree has finished
     const int32_t *e_spec_at = nullptr;
-    if (!host_pages) {
+    if (p->f >= 1.0 && all_device_single(mx)) {
+        // every row trains: its fixed-point pair comes from margin and label
+        GBT_TRY(scratch_t(c, kScrState, 1, &st_ready));
+        if (!state_ready) GBT_TRY(state_init(c, st_ready));
+    } else if (!host_pages) {
         GBT_TRY(scratch_t(c, kScrGpair, (size_t)std::max<int64_t>(n, 1) * 2, &gpair));
         if (p->f < 1.0) {
             // the gradient pass also folds the maximum of r for the sampling keys
@@ -1057,7 +1066,8 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
         uint8_t *tb;
         GBT_TRY(scratch_t(c, kScrSlotTbl, col_off + (size_t)R * G * sizeof(uint16_t), &tb));
         uint16_t *tc = (uint16_t *)(tb + col_off);
-        GBT_TRY(sparse_slot_table(c, mx, groups_d, G, so.page, R, tb, tc));
+        // 130 us for 2 M rows of 20 entries: once per call where the page stays
+        if (!(so.alias && spec_prev)) GBT_TRY(sparse_slot_table(c, mx, groups_d, G, so.page, R, tb, tc));
         stbl = SlotTable{tb, tc, (const uint8_t *)mx->groups_d + fg_off, R, rs, 0};
     }
     // dense pages: the partition reads each row's split symbol from a column
@@ -1853,9 +1863,9 @@ gbt_status gbt_train_trees(gbt_ctx *c, const gbt_matrix *data, const float *labe
     void *rh, *rd;
     GBT_TRY(tree_io(c, (size_t)S * rb, &rh, &rd));
     std::vector<TreePending> pend((size_t)S);
-    // sampled trees on device pages: each tree's last kernel resets the
-    // sampling state for the next
-    const bool carry = p->f < 1.0 && !any_host_pages(data);
+    // trees on device pages, sampled or on the one page as it is: each
+    // tree's last kernel resets the sampling state for the next
+    const bool carry = !any_host_pages(data) && (p->f < 1.0 || all_device_single(data));
     int32_t n_read = 0;
     auto read_to = [&](int32_t end) -> gbt_status {
         for (; n_read < end; ++n_read)
