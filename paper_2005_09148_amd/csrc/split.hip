@@ -1166,6 +1166,161 @@ __global__ void __launch_bounds__(kPartThreads)
     }
 }
 
+// ------------------------------------------------------------ small trees
+// A tree of few training rows spends its time on the launches of its levels,
+// not on its rows: dependent kernels of 5 to 7 us each, most of it the start
+// of a kernel and a chain of trips to memory.  k_small_level takes the place
+// of two: one block per (feature, built node) takes the node's rows whole, so
+// there are no partials to write and sum, subtracts and evaluates.  Levels of
+// few blocks use 1024 threads (a few rows per thread), others 256.  Whole
+// trees with it against the chunked passes (28 features, depth 6): 147 against
+// 177 us at 1,000 rows, 155 against 176 at 10,000, 166 against 179 at 16,384,
+// 196 against 184 at 32,768; 50 features, depth 8: 244 against 277 at 10,000,
+// 253 against 277 at 16,384, 289 against 275 at 32,768.  The block with most
+// rows sets a level's time, and a built node holds at most half of them, so
+// the limit is twice as high below the root (32,768 rows: 181 and 277 us; four
+// times as high: 209 against 194 us at 65,536).  (A partition by one block of 1024 threads, with the choice, the
+// flags, the scatter and the plan in one kernel, took 21.6 us against 11.6 us
+// for the two kernels over all CUs.)
+template <bool kRows, int kT>
+__global__ void __launch_bounds__(kT)
+    k_small_level(const uint32_t *__restrict__ page, Geo geo, const longlong2 *__restrict__ q,
+                  const int32_t *__restrict__ rows, const HistWork *__restrict__ work,
+                  const HistReduce *__restrict__ red, const int32_t *__restrict__ n_red_d,
+                  const longlong2 *__restrict__ parent, longlong2 *__restrict__ hist, int64_t total_bins,
+                  const EvalNode *__restrict__ ev, EvalParams ep, EvalCand *__restrict__ cand,
+                  unsigned long long *__restrict__ n_updates, ColCopy cols)
+{
+    __shared__ unsigned long long sg[256], sh[256];
+    __shared__ longlong2 hb[256], hs[256];
+    __shared__ unsigned int s_cnt[kT / 64];
+    // the node's records are requested with the count of nodes, not after it
+    const HistWork wk = work[blockIdx.y];
+    const HistReduce rd = red[blockIdx.y];
+    if (n_red_d && (int32_t)blockIdx.y >= *n_red_d) return;
+    const int32_t f = blockIdx.x, m = gridDim.x;
+    const int32_t b0 = geo.bin_ptr[f], B = geo.bin_ptr[f + 1] - b0;
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const bool sib = rd.sub_target >= 0;
+    longlong2 pv = make_longlong2(0, 0);
+    if (sib && t < B) pv = parent[(int64_t)rd.sub_parent * total_bins + b0 + t];
+    const int32_t slot = wid == 0 ? rd.slot : rd.sub_target;
+    EvalNode nd{0, 0, 0, 0};
+    if (wid == 0 || (wid == 1 && sib)) nd = ev[slot];
+    if (ep.e_dev) {
+        ep.e_g = ep.e_dev[0];
+        ep.e_h = ep.e_dev[1];
+    }
+    if (t < 256) sg[t] = sh[t] = 0ull;
+    __syncthreads();
+    // the feature's symbol lies within two words of a row
+    const uint32_t bit = (uint32_t)f * (uint32_t)geo.w, sft = bit & 31u;
+    const int32_t k0 = (int32_t)(bit >> 5), k1 = min(k0 + 1, geo.row_words - 1);
+    unsigned int cnt = 0;
+    constexpr int kU = 4;  // rows in flight per thread
+    for (int64_t i0 = wk.begin; i0 < wk.end; i0 += kT * kU) {
+        int64_t r[kU];
+        bool in[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int64_t i = i0 + u * kT + t;
+            in[u] = i < wk.end;
+            r[u] = in[u] ? (kRows ? (int64_t)rows[i] : i) : 0;
+        }
+        longlong2 v[kU];
+        uint32_t w0[kU], w1[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (in[u]) {
+                const uint32_t *p = page + r[u] * geo.row_words;
+                v[u] = q[r[u]];
+                w0[u] = p[k0];
+                w1[u] = p[k1];
+            } else {
+                v[u] = make_longlong2(0, 0);
+                w0[u] = w1[u] = 0u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint32_t sym = __builtin_amdgcn_alignbit(w1[u], w0[u], sft) & geo.mask;
+            const bool ok = in[u] && sym != geo.null_sym;
+            cnt += (unsigned int)__popcll(__ballot(ok));
+            if (!kRows && cols.p && in[u]) {
+                const int64_t e = (int64_t)f * cols.stride + r[u];
+                if (cols.bytes == 1)
+                    ((uint8_t *)cols.p)[e] = col_byte(sym, geo.null_sym);
+                else
+                    ((uint16_t *)cols.p)[e] = (uint16_t)sym;
+            }
+            if (ok && sym < (uint32_t)B) {
+                atomicAdd(&sg[sym], (unsigned long long)v[u].x);
+                atomicAdd(&sh[sym], (unsigned long long)v[u].y);
+            }
+        }
+    }
+    if (lane == 0) s_cnt[wid] = cnt;
+    __syncthreads();
+    if (n_updates && t == 0) {
+        unsigned long long c = 0;
+        for (int w = 0; w < kT / 64; ++w) c += s_cnt[w];
+        if (c) atomicAdd(&n_updates[((blockIdx.y * m + f) % kUpdCounters) * kUpdStride], c);
+    }
+    if (t < B) {
+        const longlong2 bv = make_longlong2((long long)sg[t], (long long)sh[t]);
+        if (hist) hist[(int64_t)rd.slot * total_bins + b0 + t] = bv;
+        hb[t] = bv;
+        if (sib) {
+            const longlong2 sv = make_longlong2(pv.x - bv.x, pv.y - bv.y);
+            if (hist) hist[(int64_t)rd.sub_target * total_bins + b0 + t] = sv;
+            hs[t] = sv;
+        }
+    }
+    __syncthreads();
+    if (wid > (sib ? 1 : 0)) return;
+    EvalCand o{0.0, 0, 0, f, -1, 0, 0};
+    if (B >= 2) {
+        const Cand cb = eval_feature(wid == 0 ? hb : hs, B, nd.sum_g, nd.sum_h, ep);
+        if (cb.valid) {
+            o.valid = 1;
+            o.gain = cb.gain;
+            o.split_bin = cb.order >> 1;
+            o.default_left = cb.order & 1;
+            o.lg = cb.lg;
+            o.lh = cb.lh;
+        }
+    }
+    if (lane == 0) cand[(int64_t)slot * m + f] = o;
+}
+
+bool small_level_fits(const gbt_matrix *mx, int64_t R, int32_t level)
+{
+    // below the root a level's built nodes hold at most R / 2 rows in all
+    if (mx->sparse || R <= 0 || R > (level ? 2 * kSmallRows : kSmallRows)) return false;
+    for (int32_t f = 0; f < mx->m; ++f)
+        if (mx->bin_ptr_h[f + 1] - mx->bin_ptr_h[f] > 256) return false;
+    return true;
+}
+
+gbt_status small_level(gbt_ctx *c, const gbt_matrix *mx, const uint32_t *page, const int64_t *q, const int32_t *rows,
+                       const HistWork *work, const HistReduce *red, const int32_t *n_red_d, int32_t max_red,
+                       const int64_t *parent, int64_t *hist, const EvalNode *ev, const EvalParams &ep, EvalCand *cand,
+                       unsigned long long *upd, const ColCopy &cols)
+{
+    const dim3 grid((unsigned)mx->m, (unsigned)max_red);
+    const int mark = timer_begin(c, kPhHist);
+    // two blocks of 1024 threads per CU, or more blocks of 256
+    const int threads = (int64_t)mx->m * max_red <= 2 * kCUs ? 1024 : 256;
+    auto kfn = threads == 1024 ? (rows ? k_small_level<true, 1024> : k_small_level<false, 1024>)
+                               : (rows ? k_small_level<true, 256> : k_small_level<false, 256>);
+    kfn<<<grid, threads, 0, c->stream>>>(page, geo_of(mx), (const longlong2 *)q, rows, work, red, n_red_d,
+                                         (const longlong2 *)parent, (longlong2 *)hist, mx->total_bins, ev, ep, cand,
+                                         upd, cols);
+    GBT_LAUNCHED();
+    timer_end(c, mark);
+    return GBT_OK;
+}
+
 // Exclusive offsets of the partition's tile counts, by one block: each
 // thread sums a contiguous run of counts, the block scans the run totals,
 // and each thread writes its run's offsets.

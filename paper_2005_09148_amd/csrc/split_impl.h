@@ -108,6 +108,20 @@ gbt_status partition_rev_impl(gbt_ctx *c, const gbt_matrix *mx, const uint32_t *
                               const SlotTable *stbl, const ColCopy &cols, const PlanArgs &plan,
                               bool order, bool root);
 
+// ---- levels of few rows: histograms and evaluation in one kernel (split.hip)
+constexpr int64_t kSmallRows = 16384;  // training rows up to which the root level takes it
+// Whether that level of a tree of R training rows of mx takes it (dense
+// pages, features of at most 256 bins).
+bool small_level_fits(const gbt_matrix *mx, int64_t R, int32_t level);
+// The histograms of the reduce items' built nodes, each from its one work
+// item's rows (count *n_red_d, at most max_red), their siblings, and every
+// feature's candidates of both (what a histogram pass and reduce_eval_impl
+// give; the plan makes one work item per node when PlanArgs::items is 1); cols: also write the page's column copy (rows NULL).
+gbt_status small_level(gbt_ctx *c, const gbt_matrix *mx, const uint32_t *page, const int64_t *q, const int32_t *rows,
+                       const HistWork *work, const HistReduce *red, const int32_t *n_red_d, int32_t max_red,
+                       const int64_t *parent, int64_t *hist, const EvalNode *ev, const EvalParams &ep, EvalCand *cand,
+                       unsigned long long *upd, const ColCopy &cols);
+
 // Whether a page of mx's geometry takes a column copy (dense, symbols of at
 // most 16 bits).
 bool split_columns_fit(const gbt_matrix *mx);

@@ -1009,6 +1009,11 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
     // a level builds more than items / 2 nodes: then up to items plus the
     // node count)
     const int32_t items = (int32_t)std::max<int64_t>(1, twg / G);
+    // levels of few rows per node take each built node's rows whole, below (a
+    // forced histogram kernel is used instead)
+    auto small_at = [&](int32_t level) {
+        return c->hist_kernel == GBT_HIST_AUTO && level < D && small_level_fits(mx, R, level);
+    };
     // the level plan scans its pass's chunk counts (at most items plus a
     // block of nodes) in 16 bits
     GBT_CHECK(items < (1 << 14), "%d work items per group", items);
@@ -1018,7 +1023,7 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
     const size_t o_cnt = o_ev1 + o_ev1;
     // the root histogram: R rows in chunks, at most `items` - 1 per group
     const int64_t root_chunk =
-        std::max<int64_t>(2048, (R + std::max(items - 1, 1) - 1) / std::max(items - 1, 1));
+        small_at(0) ? R : std::max<int64_t>(2048, (R + std::max(items - 1, 1) - 1) / std::max(items - 1, 1));
     const int32_t n_root = (int32_t)std::max<int64_t>(1, (R + root_chunk - 1) / root_chunk);
     const int32_t max_items = std::max(max_work, n_root);
     const size_t o_work = o_cnt + 256;
@@ -1102,7 +1107,8 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
         cols = cc;
     }
     int64_t *partials = nullptr;
-    GBT_TRY(scratch(c, kScrPartialsDev, (size_t)std::max(max_items, 1) * mx->total_bins * 16, (void **)&partials));
+    if (!small_at(0))
+        GBT_TRY(scratch(c, kScrPartialsDev, (size_t)std::max(max_items, 1) * mx->total_bins * 16, (void **)&partials));
     // the root's slot arrays only for a tree without levels (whose leaves
     // may be added at the slots' rows); the root level's partition takes
     // slot i as row i of node 0 without reading them
@@ -1126,7 +1132,12 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
     if (fused) GBT_TRY(scratch_t(c, kScrCand, (size_t)max_level_nodes * std::max(mx->m, 1), &cand));
     int32_t hist_launches = 0;
     int32_t *cntA = cnt, *cntB = cnt + 1;
-    if (D > 0 && R > 0) {
+    if (small_at(0)) {
+        GBT_TRY(small_level(c, mx, so.page, so.q, nullptr, work_d, red_d, nullptr, 1, nullptr, histA, evA, ep, cand,
+                            upd, cols_root));
+        if (!choose) GBT_TRY(eval_reduce_impl(c, mx, cand, mx->m, evA, 1, cntA, splits_d, nodes));
+        ++hist_launches;
+    } else if (D > 0 && R > 0) {
         HistLaunch hl{hp.kind, groups_d, G, hp.max_groups_bins, work_d, nullptr, n_root, red_d, nullptr,
                       fused ? 0 : 1, partials, stbl.row, stbl.row_stride};
         hl.cols = cols_root;  // the root's work items cover rows [0, R) once per group
@@ -1157,7 +1168,7 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
         // the partition's second kernel also plans the next level (and
         // after the last level makes the leaves)
         const bool last = d + 1 == D;
-        PlanArgs pa{evA, cntA, plan_next ? 1 : 0, items, evB, cntB, work_d, cnt + 2, red_d, cnt + 3, stat};
+        PlanArgs pa{evA, cntA, plan_next ? 1 : 0, small_at(d + 1) ? 1 : items, evB, cntB, work_d, cnt + 2, red_d, cnt + 3, stat};
         if (last) pa.lv = LeafArgs{leaf, compact, e_dev, p->lambda, p->eta, NN, 0};
         GBT_TRY(partition_rev_impl(c, mx, so.page, rows, R, slot_node, slot_tmp, nodes, rows_tmp,
                                    choose ? &lc : nullptr, stbl.row ? &stbl : nullptr, cols, pa,
@@ -1165,7 +1176,15 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
         std::swap(rows, rows_tmp);
         std::swap(slot_node, slot_tmp);
         timer_end(c, mark);
-        if (plan_next) {
+        if (plan_next && small_at(d + 1)) {
+            // the deepest evaluated level's histograms are nobody's parents
+            GBT_TRY(small_level(c, mx, so.page, so.q, rows, work_d, red_d, cnt + 3, maxn, histA,
+                                d + 2 < D ? histB : nullptr, evB, ep, cand, upd, ColCopy{}));
+            if (!choose)
+                GBT_TRY(eval_reduce_impl(c, mx, cand, mx->m, evB, std::min(2 * maxn, max_level_nodes), cntB, splits_d,
+                                         nodes));
+            ++hist_launches;
+        } else if (plan_next) {
             HistLaunch hl{hp.kind, groups_d, G, hp.max_groups_bins, work_d, cnt + 2, max_work, red_d, cnt + 3,
                           fused ? 0 : maxn, partials, stbl.row, stbl.row_stride};
             GBT_TRY(hist_launch_device(c, mx, so.page, so.q, rows, hl, histA, histB, upd));
@@ -1180,6 +1199,8 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
                 if (!choose) GBT_TRY(eval_reduce_impl(c, mx, cand, mx->m, evB, nxt, cntB, splits_d, nodes));
                 timer_end(c, mark);
             }
+        }
+        if (plan_next) {
             std::swap(histA, histB);
             std::swap(evA, evB);
             std::swap(cntA, cntB);

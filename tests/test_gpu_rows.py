@@ -30,3 +30,35 @@ def test_unaligned_rows(n, loss, off):
         outs.append([t.nodes.tobytes() for t in trees] + [margin.cpu().numpy().tobytes()])
     assert outs[0] == outs[1]
     ctx.close()
+
+
+@pytest.mark.parametrize("n,m,max_bin,depth,f", [
+    (16_384, 5, 256, 5, 1.0), (16_385, 5, 256, 5, 1.0), (32_768, 3, 64, 6, 1.0), (32_769, 3, 64, 6, 1.0),
+    (40_000, 29, 256, 4, 0.4), (1025, 130, 32, 4, 1.0), (3000, 70, 17, 8, 1.0), (255, 2, 2, 3, 1.0),
+    (20_000, 4, 300, 4, 0.5)])
+@pytest.mark.parametrize("loss", [0, 1])
+def test_small_levels(n, m, max_bin, depth, f, loss):
+    """The one-kernel histogram and evaluation of levels of few rows around its
+    limits (rows, blocks of 1024 or 256 threads, above 128 features, above
+    256 bins), against the chunked passes with the histogram kernel forced."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2005_09148_amd import gbt
+    r = np.random.default_rng(n + m)
+    X = r.normal(size=(n, m)).astype(np.float32)
+    X[r.random(X.shape) < 0.1] = np.nan
+    X[:, -1] = np.floor(X[:, -1])
+    y = torch.from_numpy((np.nan_to_num(X[:, 0]) + r.normal(size=n) > 0).astype(np.float32)).cuda()
+    ctx = gbt.Context(0)
+    mx = gbt.gbt_quantize(ctx, X, max_bin=max_bin)
+    P = gbt.make_train_params(loss=loss, max_depth=depth, eta=0.3, f=f)
+    outs = []
+    for kernel in (ctx.HIST_AUTO, ctx.HIST_PLAIN):
+        ctx.set_hist_kernel(kernel)
+        margin = torch.zeros(n, device="cuda")
+        trees = gbt.gbt_train_trees(ctx, mx, y, margin, P, 2)
+        stats = [(t.stats.hist_updates, t.stats.hist_rows, t.stats.hist_bytes, t.stats.hist_launches,
+                  t.stats.hist_cols) for t in trees]
+        outs.append([t.nodes.tobytes() for t in trees] + [margin.cpu().numpy().tobytes(), stats])
+    assert outs[0] == outs[1]
+    ctx.close()
