@@ -313,99 +313,6 @@ __global__ void __launch_bounds__(kEvalThreads)
 }
 
 // ------------------------------------------------------------ reduce + evaluate
-// One block per (feature, reduce item): 4 waves cover the feature's bins 64
-// at a time, and kSub such wave sets take every kSub-th partial; the built
-// node's and the sibling's bins go to hist (unless hist is NULL: the level's
-// histograms are parents of no later level) and to LDS, then wave 0
-// evaluates the built node and wave 1 the sibling on the LDS copy.  Levels
-// of few nodes and many partials per node use kSub = 4 (1024 threads);
-// levels of many nodes use kSub = 1 (256 threads), so that more blocks are
-// resident while two waves of each evaluate.
-template <int kSub>
-__global__ void __launch_bounds__(256 * kSub)
-    k_reduce_eval(const longlong2 *__restrict__ partials, const HistReduce *__restrict__ red,
-                  const int32_t *__restrict__ n_red_d, const longlong2 *__restrict__ parent,
-                  longlong2 *__restrict__ hist, int64_t total_bins, const int32_t *__restrict__ bin_ptr,
-                  int32_t m, const EvalNode *__restrict__ ev, EvalParams ep, EvalCand *__restrict__ cand)
-{
-    if (n_red_d && (int32_t)blockIdx.y >= *n_red_d) return;
-    __shared__ longlong2 hb[256], hs[256];
-    __shared__ long long sg[kSub][256], sh[kSub][256];
-    const HistReduce rd = red[blockIdx.y];
-    const int32_t f = blockIdx.x;
-    const int32_t b0 = bin_ptr[f], B = bin_ptr[f + 1] - b0;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int sub = wid >> 2;                 // partial subset
-    const int32_t b = (wid & 3) * 64 + lane;  // bin of the feature (B <= 256)
-    const bool sib = rd.sub_target >= 0;
-    long long g = 0, h = 0;
-    if (b < B) {
-        const longlong2 *src = partials + (int64_t)rd.part0 * total_bins + b0 + b;
-        int32_t k = sub;
-        // eight loads in flight per thread
-        for (; k + 7 * kSub < rd.nparts; k += 8 * kSub) {
-            longlong2 v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = src[(int64_t)(k + j * kSub) * total_bins];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                g += v[j].x;
-                h += v[j].y;
-            }
-        }
-        for (; k < rd.nparts; k += kSub) {
-            const longlong2 v = src[(int64_t)k * total_bins];
-            g += v.x;
-            h += v.y;
-        }
-    }
-    sg[sub][b] = g;
-    sh[sub][b] = h;
-    __syncthreads();
-    if (sub == 0 && b < B) {
-        for (int t = 1; t < kSub; ++t) {
-            g += sg[t][b];
-            h += sh[t][b];
-        }
-        const longlong2 bv = make_longlong2(g, h);
-        if (hist) hist[(int64_t)rd.slot * total_bins + b0 + b] = bv;
-        hb[b] = bv;
-        if (sib) {
-            const longlong2 pv = parent[(int64_t)rd.sub_parent * total_bins + b0 + b];
-            const longlong2 sv = make_longlong2(pv.x - g, pv.y - h);
-            if (hist) hist[(int64_t)rd.sub_target * total_bins + b0 + b] = sv;
-            hs[b] = sv;
-        }
-    }
-    __syncthreads();
-    if (wid > (sib ? 1 : 0)) return;
-    const int32_t slot = wid == 0 ? rd.slot : rd.sub_target;
-    if (ep.e_dev) {
-        ep.e_g = ep.e_dev[0];
-        ep.e_h = ep.e_dev[1];
-    }
-    EvalCand o;
-    o.valid = 0;
-    o.gain = 0.0;
-    o.feature = f;
-    o.split_bin = -1;
-    o.default_left = 0;
-    o.lg = o.lh = 0;
-    if (B >= 2) {
-        const EvalNode nd = ev[slot];
-        const Cand cb = eval_feature(wid == 0 ? hb : hs, B, nd.sum_g, nd.sum_h, ep);
-        if (cb.valid) {
-            o.valid = 1;
-            o.gain = cb.gain;
-            o.split_bin = cb.order >> 1;
-            o.default_left = cb.order & 1;
-            o.lg = cb.lg;
-            o.lh = cb.lh;
-        }
-    }
-    if (lane == 0) cand[(int64_t)slot * m + f] = o;
-}
-
 // Best split of one feature of at most 64 kBL bins for one node, held in
 // registers: lane l's t-th value is bin t * 64 + l (zeros past B).  The same
 // cuts, gains and choice as eval_feature.
@@ -449,14 +356,154 @@ __device__ Cand eval_feature_regs(const long long *g, const long long *h, int32_
     return wave_best(best);
 }
 
+// One block per (feature, reduce item): kBL waves cover the feature's bins
+// (at most 64 kBL) 64 at a time, and kSub such wave sets take every kSub-th
+// partial.  Then set 0 has the built node's bins and set 1 the sibling's
+// (parent minus the sums): each writes its bins to hist (unless hist is
+// NULL: the level's histograms are parents of no later level) and evaluates
+// them, a wave per 64 bins, two candidates per lane.
+//
+// Levels of few (feature, node) pairs are bound by the chain of one wave's
+// requests for the partials, so a block has 1024 threads whatever the
+// features' width (kSub kBL = 16; 128 rows of 64 bins requested at once),
+// and what the evaluation needs is requested before the partials.  us per
+// launch, against the register form that features of at most 64 bins had
+// here before: 12 features of 64 bins, 1M rows, root and levels of 1, 2, 4,
+// 8 built nodes 8.8, 11.1, 6.6, 7.5, 5.2 (134, 135, 66, 36, 25); 37 features,
+// 233k rows 5.5, 5.5, 4.6, 4.2, 4.9 (37, 36, 21, 15, 13).  28 features of 256
+// bins, 1M rows, with the evaluation in one wave per node before: 11.4 (12.3)
+// at the root, 8.8 (11.4) at 16 nodes; the root's partials are 58 MB, 5 TB/s.
+template <int kSub, int kBL>
+__global__ void __launch_bounds__(64 * kSub * kBL)
+    k_reduce_eval(const longlong2 *__restrict__ partials, const HistReduce *__restrict__ red,
+                  const int32_t *__restrict__ n_red_d, const longlong2 *__restrict__ parent,
+                  longlong2 *__restrict__ hist, int64_t total_bins, const int32_t *__restrict__ bin_ptr,
+                  int32_t m, const EvalNode *__restrict__ ev, EvalParams ep, EvalCand *__restrict__ cand)
+{
+    static_assert(kSub >= 2, "sets 0 and 1 evaluate the node and its sibling");
+    if (n_red_d && (int32_t)blockIdx.y >= *n_red_d) return;
+    __shared__ long long sg[kSub][64 * kBL], sh[kSub][64 * kBL];
+    __shared__ long long s_tg[2][kBL], s_th[2][kBL];  // totals of each 64 bins
+    __shared__ Cand s_best[2][kBL];
+    const HistReduce rd = red[blockIdx.y];
+    const int32_t f = blockIdx.x;
+    const int32_t b0 = bin_ptr[f], B = bin_ptr[f + 1] - b0;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int sub = wid / kBL, part = wid % kBL;  // partial subset, 64-bin part
+    const int32_t b = part * 64 + lane;           // bin of the feature (B <= 64 kBL)
+    // the waves that evaluate, and what they need besides the sums
+    const bool mine = sub == 0 || (sub == 1 && rd.sub_target >= 0);
+    const int32_t slot = sub == 0 ? rd.slot : rd.sub_target;
+    longlong2 pv = make_longlong2(0, 0);
+    EvalNode nd{};
+    if (mine) {
+        if (sub == 1 && b < B) pv = parent[(int64_t)rd.sub_parent * total_bins + b0 + b];
+        nd = ev[slot];
+        if (ep.e_dev) {
+            ep.e_g = ep.e_dev[0];
+            ep.e_h = ep.e_dev[1];
+        }
+    }
+    long long g = 0, h = 0;
+    if (b < B) {
+        const longlong2 *src = partials + (int64_t)rd.part0 * total_bins + b0 + b;
+        int32_t k = sub;
+        // eight loads in flight per thread
+        for (; k + 7 * kSub < rd.nparts; k += 8 * kSub) {
+            longlong2 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = src[(int64_t)(k + j * kSub) * total_bins];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                g += v[j].x;
+                h += v[j].y;
+            }
+        }
+        for (; k < rd.nparts; k += kSub) {
+            const longlong2 v = src[(int64_t)k * total_bins];
+            g += v.x;
+            h += v.y;
+        }
+    }
+    sg[sub][b] = g;
+    sh[sub][b] = h;
+    __syncthreads();
+    long long xg = 0, xh = 0;  // inclusive prefix sums over the wave's bins
+    if (mine) {
+        g = h = 0;
+#pragma unroll
+        for (int t = 0; t < kSub; ++t) {
+            g += sg[t][b];
+            h += sh[t][b];
+        }
+        if (sub == 1) {
+            g = pv.x - g;
+            h = pv.y - h;
+        }
+        if (hist && b < B) hist[(int64_t)slot * total_bins + b0 + b] = make_longlong2(g, h);
+        xg = g;
+        xh = h;
+        wave_scan2(xg, xh);
+        if (lane == 63) {
+            s_tg[sub][part] = xg;
+            s_th[sub][part] = xh;
+        }
+    }
+    __syncthreads();
+    if (mine) {
+        long long tg = 0, th = 0;  // the feature's totals
+#pragma unroll
+        for (int t = 0; t < kBL; ++t) {
+            const long long vg = s_tg[sub][t], vh = s_th[sub][t];
+            if (t < part) {
+                xg += vg;
+                xh += vh;
+            }
+            tg += vg;
+            th += vh;
+        }
+        const double G = fx(nd.sum_g, ep.e_g), H = fx(nd.sum_h, ep.e_h);
+        const long long mg = nd.sum_g - tg, mh = nd.sum_h - th;
+        const long long lg[2] = {xg, xg + mg}, lh[2] = {xh, xh + mh};
+        const int32_t s[1] = {b + 1};  // left = bins < s
+        Cand best;
+        best.valid = 0;
+        best.gain = 0.0;
+        best.order = 0;
+        best.lg = best.lh = 0;
+        pick_candidates<2>(lg, lh, s, B, nd.sum_g, nd.sum_h, (G * G) / (H + ep.lambda), ep, best);
+        best = wave_best(best);
+        if (lane == 0) s_best[sub][part] = best;
+    }
+    __syncthreads();
+    if (!mine || part != 0 || lane != 0) return;
+    Cand cb = s_best[sub][0];
+    for (int t = 1; t < kBL; ++t)
+        if (better(s_best[sub][t], cb)) cb = s_best[sub][t];
+    EvalCand o;
+    o.valid = cb.valid;
+    o.gain = cb.valid ? cb.gain : 0.0;
+    o.feature = f;
+    o.split_bin = cb.valid ? cb.order >> 1 : -1;
+    o.default_left = cb.valid ? cb.order & 1 : 0;
+    o.lg = cb.valid ? cb.lg : 0;
+    o.lh = cb.valid ? cb.lh : 0;
+    cand[(int64_t)slot * m + f] = o;
+}
+
 // k_reduce_eval with the histograms in registers: a wave takes 4 / kBL
 // features of one node (features of at most 64 kBL bins), lane l bins
 // l, l + 64, ...; the parent's and the partials' loads of all of them are
 // in flight together.  No LDS and no block barrier.  blockIdx.z = 0 sums the
 // built node's partials, writes its histogram and evaluates it; z = 1 does
 // the same for its sibling (parent minus the sums), so the two evaluations
-// run side by side.
-template <int kBL>
+// run side by side.  kBoth (no z): one wave does the one and then the other,
+// which reads the partials once.  Wide levels are bound by these bytes: at
+// 2000 features of 64 bins and 16 / 32 / 64 / 128 / 256 built nodes 50 / 78 /
+// 123 / 189 / 247 us against 54 / 86 / 139 / 232 / 281 (the last 4.2 TB/s);
+// levels of fewer blocks have waves to spare and lose by the longer chain
+// (50 features of 256 bins and 64 nodes: 22.6 us against 19.6).
+template <int kBL, bool kBoth>
 __global__ void __launch_bounds__(256)
     k_reduce_eval_regs(const longlong2 *__restrict__ partials, const HistReduce *__restrict__ red,
                        const int32_t *__restrict__ n_red_d, const longlong2 *__restrict__ parent,
@@ -488,7 +535,7 @@ __global__ void __launch_bounds__(256)
     longlong2 pv[kV];
 #pragma unroll
     for (int i = 0; i < kV; ++i)
-        pv[i] = (which == 1 && off[i] >= 0) ? parent[(int64_t)rd.sub_parent * total_bins + off[i]]
+        pv[i] = ((which == 1 || (kBoth && sib)) && off[i] >= 0) ? parent[(int64_t)rd.sub_parent * total_bins + off[i]]
                                             : make_longlong2(0, 0);
     long long g[kV], h[kV];
 #pragma unroll
@@ -526,17 +573,17 @@ __global__ void __launch_bounds__(256)
             h[i] = pv[i].y - h[i];
         }
     }
-    const int32_t slot = which == 0 ? rd.slot : rd.sub_target;
-    if (hist) {
-#pragma unroll
-        for (int i = 0; i < kV; ++i)
-            if (off[i] >= 0) hist[(int64_t)slot * total_bins + off[i]] = make_longlong2(g[i], h[i]);
-    }
     if (ep.e_dev) {
         ep.e_g = ep.e_dev[0];
         ep.e_h = ep.e_dev[1];
     }
-    {
+    int32_t slot = which == 0 ? rd.slot : rd.sub_target;
+    for (;;) {
+        if (hist) {
+#pragma unroll
+            for (int i = 0; i < kV; ++i)
+                if (off[i] >= 0) hist[(int64_t)slot * total_bins + off[i]] = make_longlong2(g[i], h[i]);
+        }
         const EvalNode nd = ev[slot];
 #pragma unroll
         for (int j = 0; j < kFW; ++j) {
@@ -562,6 +609,13 @@ __global__ void __launch_bounds__(256)
                 }
             }
             if (lane == 0) cand[(int64_t)slot * m + f] = o;
+        }
+        if (!kBoth || !sib || slot == rd.sub_target) break;
+        slot = rd.sub_target;
+#pragma unroll
+        for (int i = 0; i < kV; ++i) {
+            g[i] = pv[i].x - g[i];
+            h[i] = pv[i].y - h[i];
         }
     }
 }
@@ -627,17 +681,26 @@ gbt_status reduce_eval_impl(gbt_ctx *c, const gbt_matrix *mx, const int64_t *par
     int32_t max_feature_bins = 0;
     for (int32_t f = 0; f < mx->m; ++f)
         max_feature_bins = std::max(max_feature_bins, mx->bin_ptr_h[f + 1] - mx->bin_ptr_h[f]);
-    // features of at most 64 bins, or many (feature, node) pairs: the
-    // register form (a wave per 1, 2 or 4 features)
-    const int kbl = max_feature_bins <= 64 ? 1 : max_feature_bins <= 128 ? 2 : max_feature_bins <= 256 ? 4 : 0;
-    if (kbl == 1 || (kbl > 0 && (int64_t)max_red * mx->m >= 2 * kCUs)) {
+    GBT_CHECK(max_feature_bins <= 256, "the fused evaluation holds features of at most 256 bins");
+    const int kbl = max_feature_bins <= 64 ? 1 : max_feature_bins <= 128 ? 2 : 4;
+    // The line between the block and the register form, us (block / register):
+    // features of at most 64 bins 8.2 / 12.4 at 800 pairs, 10.7 / 12.4 at 1536
+    // and 11.7 / 10.9 at 1600; 128 bins 9.3 / 15.0 at 800, 11.8 / 14.5 at 1536
+    // and 13.2 / 12.4 at 1600; 256 bins 9.0 / 11.8 at 400, 10.8 / 11.0 at 768
+    // and 12.5 / 11.9 at 800.
+    const int64_t pairs = (int64_t)max_red * mx->m;
+    if (pairs >= (kbl == 4 ? 3 : 6) * kCUs) {
         const int fpb = 4 * (4 / kbl);  // features per block
-        // z: the built node and, below the root, its sibling
-        dim3 gr((unsigned)((mx->m + fpb - 1) / fpb), (unsigned)max_red, parent ? 2u : 1u);
+        const unsigned gx = (unsigned)((mx->m + fpb - 1) / fpb);
+        // enough blocks to fill the chip several times: one wave evaluates
+        // both nodes; otherwise z: the built node and, below the root, its
+        // sibling (figures at the kernel)
+        const bool both = parent && (int64_t)gx * max_red >= 7 * kCUs;
+        dim3 gr(gx, (unsigned)max_red, parent && !both ? 2u : 1u);
 #define GBT_REG_EVAL(BL)                                                                                       \
-    k_reduce_eval_regs<BL><<<gr, 256, 0, c->stream>>>((const longlong2 *)partials, red, n_red_d,           \
-                                                      (const longlong2 *)parent, (longlong2 *)hist,         \
-                                                      mx->total_bins, mx->bin_ptr_d, mx->m, ev, ep, cand)
+    (both ? k_reduce_eval_regs<BL, true> : k_reduce_eval_regs<BL, false>)<<<gr, 256, 0, c->stream>>>(        \
+        (const longlong2 *)partials, red, n_red_d, (const longlong2 *)parent, (longlong2 *)hist, mx->total_bins, \
+        mx->bin_ptr_d, mx->m, ev, ep, cand)
         if (kbl == 1)
             GBT_REG_EVAL(1);
         else if (kbl == 2)
@@ -649,15 +712,17 @@ gbt_status reduce_eval_impl(gbt_ctx *c, const gbt_matrix *mx, const int64_t *par
         return GBT_OK;
     }
     dim3 grid((unsigned)mx->m, (unsigned)max_red);
-    // many (feature, node) blocks: the narrow form keeps more of them resident
-    if ((int64_t)max_red * mx->m >= 2 * kCUs)
-        k_reduce_eval<1><<<grid, 256, 0, c->stream>>>((const longlong2 *)partials, red, n_red_d,
-                                                      (const longlong2 *)parent, (longlong2 *)hist,
-                                                      mx->total_bins, mx->bin_ptr_d, mx->m, ev, ep, cand);
+#define GBT_BLOCK_EVAL(SUB, BL)                                                                                \
+    k_reduce_eval<SUB, BL><<<grid, 64 * SUB * BL, 0, c->stream>>>((const longlong2 *)partials, red, n_red_d, \
+                                                                  (const longlong2 *)parent, (longlong2 *)hist, \
+                                                                  mx->total_bins, mx->bin_ptr_d, mx->m, ev, ep, cand)
+    if (kbl == 1)
+        GBT_BLOCK_EVAL(16, 1);
+    else if (kbl == 2)
+        GBT_BLOCK_EVAL(8, 2);
     else
-        k_reduce_eval<4><<<grid, 1024, 0, c->stream>>>((const longlong2 *)partials, red, n_red_d,
-                                                       (const longlong2 *)parent, (longlong2 *)hist,
-                                                       mx->total_bins, mx->bin_ptr_d, mx->m, ev, ep, cand);
+        GBT_BLOCK_EVAL(4, 4);
+#undef GBT_BLOCK_EVAL
     GBT_LAUNCHED();
     return GBT_OK;
 }
