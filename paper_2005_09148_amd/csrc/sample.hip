@@ -375,10 +375,13 @@ __device__ inline bool thresh_ok(unsigned long long F, unsigned long long C, int
     return hi != 0 || lo >= F;
 }
 
-// One block of 256 threads: evaluate every bucket boundary, keep the least
-// one that satisfies cond, descend into the bucket below it, clear the
-// histogram for the next level.
-__global__ void __launch_bounds__(256) k_mvs_radix_decide(SampleState *__restrict__ st, int64_t K,
+// One block: evaluate every bucket boundary, keep the least one that
+// satisfies cond, descend into the bucket below it, clear the histogram for
+// the next level.  Bound by the latency of one block's steps: 1024 threads
+// take two buckets each (8.7 us a level at 777,777 rows; 256 threads of
+// eight buckets 14.7).
+constexpr int kDecideThreads = 1024;
+__global__ void __launch_bounds__(kDecideThreads) k_mvs_radix_decide(SampleState *__restrict__ st, int64_t K,
                                                           unsigned long long *__restrict__ hcnt,
                                                           unsigned long long *__restrict__ hsum,
                                                           int32_t count_mode)
@@ -392,8 +395,9 @@ __global__ void __launch_bounds__(256) k_mvs_radix_decide(SampleState *__restric
     // s_f[b] = F_below + the key sums of buckets below b; s_c[b] = C_above +
     // the counts of buckets b and above (b = 0..nb): each thread takes a run
     // of kPer buckets, the block scans the runs' totals
-    constexpr int kPer = (kDigitBuckets + 255) / 256;
-    __shared__ unsigned long long s_wf[4], s_wc[4];
+    constexpr int kPer = (kDigitBuckets + kDecideThreads - 1) / kDecideThreads;
+    constexpr int kW = kDecideThreads / 64;
+    __shared__ unsigned long long s_wf[kW], s_wc[kW];
     const int b0 = (int)threadIdx.x * kPer;
     unsigned long long cnt[kPer], sum[kPer], rf = 0, rc = 0;
 #pragma unroll
@@ -413,7 +417,8 @@ __global__ void __launch_bounds__(256) k_mvs_radix_decide(SampleState *__restric
     if (threadIdx.x == 0) s_best = nb + 1;
     __syncthreads();
     unsigned long long pf = xf - rf, pc = xc - rc, ctot = 0, ftot = 0;  // exclusive prefixes; totals
-    for (int w = 0; w < 4; ++w) {
+#pragma unroll
+    for (int w = 0; w < kW; ++w) {
         if (w < wid) {
             pf += s_wf[w];
             pc += s_wc[w];
@@ -433,7 +438,7 @@ __global__ void __launch_bounds__(256) k_mvs_radix_decide(SampleState *__restric
         pc += cnt[j];
     }
     // the boundary past the last bucket, when the runs end before it
-    if (threadIdx.x == 0 && nb >= 256 * kPer) {
+    if (threadIdx.x == 0 && nb >= kDecideThreads * kPer) {
         s_f[nb] = F0 + ftot;
         s_c[nb] = C0;
     }
@@ -984,7 +989,7 @@ gbt_status threshold_rest(gbt_ctx *c, const SampleSrc &src, int kind, const int6
             k_mvs_radix_hist<kSrcMargin><<<grid, 256, 0, c->stream>>>(src, keys, n, lambda, l2, st, hist,
                                                                       hist + kDigitBuckets);
         GBT_LAUNCHED();
-        k_mvs_radix_decide<<<1, 256, 0, c->stream>>>(st, K, hist, hist + kDigitBuckets, count_mode ? 1 : 0);
+        k_mvs_radix_decide<<<1, kDecideThreads, 0, c->stream>>>(st, K, hist, hist + kDigitBuckets, count_mode ? 1 : 0);
         GBT_LAUNCHED();
     }
     return GBT_OK;
