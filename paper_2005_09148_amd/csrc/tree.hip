@@ -53,14 +53,19 @@ public:
     // behind the work queued so far: they cross the host link while the
     // kernels queued until run() is called do other work.  Nothing may use
     // the staging buffers meanwhile.  Device and disk pages: does nothing.
-    // 3 M x 100 rows in three pinned pages, f = 0.1: 7.19 ms per tree against
-    // 7.83 when the copies waited for the tree (the link carries 336 MB of
-    // pages, 5.9 ms, and the gathered sample).
+    // A kernel of a few blocks copies these: a copy engine is chosen anew for
+    // a copy that finds the last one busy, and with engine copies queued
+    // across trees every other tree got one of half the rate (in a process's
+    // second context and later ones).  Per tree, f = 0.1, against copies that
+    // wait for the tree: 3 M x 100 rows in three pages 7.68 ms (7.85), 16 M x
+    // 100 in four 39.4 (40.3); engine copies here 7.2 in the first context
+    // and 9.7 in the next.  The link carries 336 MB of the three pages,
+    // 5.9 ms, and the gathered sample.
     gbt_status ahead()
     {
         if (mx->page_home != GBT_HOME_PINNED_HOST) return GBT_OK;
         GBT_TRY(open());
-        while (issued < 2 && issued < chunks.size()) GBT_TRY(issue());
+        while (issued < 2 && issued < chunks.size()) GBT_TRY(issue(true));
         return GBT_OK;
     }
     gbt_status run(const ChunkFn &fn, double *h2d_bytes);
@@ -83,7 +88,7 @@ private:
     bool on_disk(size_t k) const { return chunks[k].pg->fd >= 0; }
     gbt_status open();
     gbt_status start_read(size_t k);
-    gbt_status issue();
+    gbt_status issue(bool by_kernel = false);
 };
 
 gbt_status PageStream::open()
@@ -157,8 +162,29 @@ gbt_status PageStream::start_read(size_t k)
     return GBT_OK;
 }
 
-// Queues the copy of the next chunk on the side stream.
-gbt_status PageStream::issue()
+constexpr int kPageCopyBlocks = 16;
+
+// Rows from pinned host memory (a row is a multiple of 16 bytes); bound by
+// the link, so a few blocks with eight loads in flight per thread do: with
+// 16, 32, 64 and 128 blocks for all copies a tree of three 1 M x 100 pages
+// took 7.66, 7.74, 7.75 and 7.92 ms.
+__global__ void __launch_bounds__(256) k_page_copy(const uint4 *__restrict__ src, uint4 *__restrict__ dst, int64_t n)
+{
+    const int64_t step = (int64_t)gridDim.x * 256;
+    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (; i + 7 * step < n; i += 8 * step) {
+        uint4 v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = src[i + j * step];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) dst[i + j * step] = v[j];
+    }
+    for (; i < n; i += step) dst[i] = src[i];
+}
+
+// Queues the copy of the next chunk on the side stream, by a kernel (pinned
+// chunks only) or a copy engine.
+gbt_status PageStream::issue(bool by_kernel)
 {
     const Chunk &ch = chunks[issued];
     int b = (int)(issued & 1);
@@ -168,7 +194,13 @@ gbt_status PageStream::issue()
         src = c->disk_stage[b];
     }
     GBT_HIP(hipStreamWaitEvent(c->side, ev.consumed[b], 0));
-    GBT_HIP(hipMemcpyAsync(buf[b], src, (size_t)ch.rows * row_bytes(), hipMemcpyHostToDevice, c->side));
+    const size_t bytes = (size_t)ch.rows * row_bytes();
+    if (by_kernel) {
+        k_page_copy<<<kPageCopyBlocks, 256, 0, c->side>>>((const uint4 *)src, (uint4 *)buf[b], (int64_t)(bytes / 16));
+        GBT_LAUNCHED();
+    } else {
+        GBT_HIP(hipMemcpyAsync(buf[b], src, bytes, hipMemcpyHostToDevice, c->side));
+    }
     GBT_HIP(hipEventRecord(ev.copied[b], c->side));
     ++issued;
     return GBT_OK;
