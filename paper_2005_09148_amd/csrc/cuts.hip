@@ -629,7 +629,8 @@ gbt_status select_cut_keys(gbt_ctx *c, const uint32_t *keys, const std::vector<i
     int64_t long_keys = 0;
     for (int32_t j = 0; j < m; ++j) {
         const int64_t len = seg[j + 1] - seg[j];
-        GBT_CHECK(len >= 0 && len < INT32_MAX, "feature %d has %lld sketch keys", j, (long long)len);
+        // keys are counted, ranked and stepped over in 32 unsigned bits
+        GBT_CHECK(len >= 0 && len <= (int64_t)UINT32_MAX - kSmall, "feature %d has %lld sketch keys", j, (long long)len);
         const CutSeg s{seg[j], len, j, 0, 0, 0};
         if (len > kSmall) {
             segs.push_back(s);

@@ -185,3 +185,19 @@ def test_csr_refuses_bad_indices(gbt, what):
         gbt.gbt_quantize(ctx, d, max_bin=16)
     assert err.value.code == gbt.GBT_E_INVALID
     ctx.close()
+
+
+def test_more_keys_than_31_bits(gbt):
+    """Ranks above 2^31 of one feature's keys: the values are i mod 1000, so
+    every rank's value is known."""
+    n, bins = (1 << 31) + 1001, 8
+    X = torch.arange(1000, dtype=torch.float32, device="cuda").repeat(n // 1000 + 1)[:n, None]
+    ctx = gbt.Context(0)
+    mx = gbt.gbt_quantize(ctx, X, max_bin=bins, sketch_max_rows=n)
+    counts = np.full(1000, n // 1000, np.int64)
+    counts[:n % 1000] += 1
+    ranks = (np.arange(1, bins, dtype=np.int64) * n + bins - 1) // bins - 1
+    want = np.searchsorted(np.cumsum(counts), ranks, side="right").astype(np.float32)
+    assert np.array_equal(mx.cuts()[1], np.unique(want))
+    mx.free()
+    ctx.close()
