@@ -514,38 +514,84 @@ __global__ void __launch_bounds__(kBigThreads)
     }
 }
 
+// Orders a wave's LDS writes before its later reads of other lanes' words.
+__device__ inline void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The keys of the buckets to be gathered, bucket by bucket (any order
 // within one): the chunk's first place in a bucket is known, so only LDS
-// cursors are needed.
+// cursors are needed.  Most cells of the index hold no gathered bucket (256
+// bins: 6 % of the keys are gathered), so a bit per cell drops most keys
+// after one LDS read; a wave lines the others up in LDS and searches them 64
+// at a time.  500 M keys of 50 features 863 us against 1026 with every key
+// searched, 28 M of 28 features 59 against 67; 40 M of 2000 features (short
+// chunks, which the bits' set-up weighs on) 101 against 94.
 __global__ void __launch_bounds__(kCountThreads)
     k_cut_gather(const uint32_t *__restrict__ keys, const CutChunk *__restrict__ chunks,
                  const CutTables *__restrict__ tables, const uint32_t *__restrict__ part,
                  const uint32_t *__restrict__ place, const int64_t *__restrict__ base, uint32_t *__restrict__ out)
 {
     __shared__ __align__(16) CutLds L;
+    __shared__ uint32_t hit[kCells / 32];
+    __shared__ uint32_t line[kCountThreads * 2];
     const CutChunk ch = chunks[blockIdx.x];
     load_tables(tables + ch.seg, &L.T);
     for (int t = threadIdx.x; t < kBuckets; t += kCountThreads) {
         const uint32_t p = place[(int64_t)ch.seg * kBuckets + t];
         L.cnt[t] = p == kNanKey ? kNanKey : p + part[(int64_t)blockIdx.x * kBuckets + t];
     }
+    if (threadIdx.x < kCells / 32) hit[threadIdx.x] = 0u;
+    __syncthreads();
+    // cell c's keys lie in buckets tab[c] .. tab[c + 1]
+    for (int c = threadIdx.x; c < kCells; c += kCountThreads) {
+        bool any = false;
+        for (int t = L.T.tab[c]; t <= L.T.tab[c + 1] && !any; ++t) any = L.cnt[t] != kNanKey;
+        if (any) atomicOr(&hit[c >> 5], 1u << (c & 31));
+    }
     __syncthreads();
     uint32_t *dst = out + base[ch.seg];
     const int32_t steps = L.T.steps;
     const float x0 = L.T.x0, scale = L.T.scale;
+    const int lane = threadIdx.x & 63;
+    uint32_t *mine = line + (threadIdx.x >> 6) * 128;  // the wave's, at most 63 kept and 64 new
+    const uint64_t below = (1ull << lane) - 1ull;
+    int32_t n = 0;  // keys in line (the same in every lane)
+    auto search = [&](uint32_t key) {
+        const uint32_t v[1] = {key};
+        int32_t b[1];
+        find_buckets(L.T, steps, x0, scale, v, b);
+        if (key != kNanKey && L.cnt[b[0]] != kNanKey) dst[atomicAdd(&L.cnt[b[0]], 1u)] = key;
+    };
     for (int64_t i0 = ch.begin; i0 < ch.end; i0 += kCountThreads * kUnroll) {
         uint32_t k[kUnroll];
-        int32_t b[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int64_t i = i0 + u * kCountThreads + threadIdx.x;
             k[u] = i < ch.end ? keys[i] : kNanKey;
         }
-        find_buckets(L.T, steps, x0, scale, k, b);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            if (k[u] != kNanKey && L.cnt[b[u]] != kNanKey) dst[atomicAdd(&L.cnt[b[u]], 1u)] = k[u];
+        for (int u = 0; u < kUnroll; ++u) {
+            const int32_t c = cell_of(k[u], x0, scale);
+            const bool take = k[u] != kNanKey && ((hit[c >> 5] >> (c & 31)) & 1u);
+            const uint64_t m = __ballot(take);
+            if (take) mine[n + __popcll(m & below)] = k[u];
+            n += __popcll(m);
+            if (n >= 64) {
+                wave_lds_fence();
+                const uint32_t key = mine[lane], rest = mine[64 + lane];
+                wave_lds_fence();
+                n -= 64;
+                if (lane < n) mine[lane] = rest;
+                search(key);
+            }
+        }
     }
+    wave_lds_fence();
+    search(lane < n ? mine[lane] : kNanKey);
 }
 
 // The ranks pk.r0 .. pk.r1 of a bucket of up to kPickThreads * kI keys.
