@@ -728,58 +728,68 @@ void free_quantizer(gbt_quantizer *q)
 }
 
 // The quantizer's nk (feature, key) pairs grouped by feature: feature j's keys
-// at [seg[j], seg[j + 1]) of the buffer `room` gives for nk keys.
+// at [seg[j], seg[j + 1]) of the buffer `room` gives for nk keys.  The blocks'
+// count tables take up to 4 bytes per pair beside that buffer; where memory
+// has no room for both, the global counters (8 bytes per feature) group the
+// pairs instead.
 template <typename Room>
 gbt_status group_by_feature(gbt_quantizer *q, int64_t nk, std::vector<int64_t> *seg, Room &&room)
 {
     gbt_ctx *c = q->ctx;
     const int32_t m = q->m;
-    seg->assign(m + 1, 0);
-    const bool lds = m <= kGroupFeats && nk < ((int64_t)1 << 32);
     // enough pairs per block to pay for its pass over the features
     const int64_t per = std::max<int64_t>((nk + kGroupBlocks - 1) / kGroupBlocks, std::max(kGroupThreads * 4, m));
     const int64_t blocks = (nk + per - 1) / per;
-    const size_t o_cnt = ((size_t)m * 8 + 255) / 256 * 256, bytes = o_cnt + (lds ? (size_t)blocks * m * 4 : 0);
-    char *w = nullptr;
-    GBT_TRY(dev_alloc(c, bytes, (void **)&w));
-    auto run = [&]() -> gbt_status {
-        unsigned long long *tot = (unsigned long long *)w;
-        uint32_t *cnt = (uint32_t *)(w + o_cnt);
-        std::vector<unsigned long long> h(m, 0ull);
-        const size_t lds_bytes = (size_t)m * 4;
-        if (nk && lds) {
-            k_group_count<<<(unsigned)blocks, kGroupThreads, lds_bytes, c->stream>>>(q->feats, nk, per, m, cnt);
-            GBT_LAUNCHED();
-            k_group_offsets<<<grid_for(m, 64), 64, 0, c->stream>>>(cnt, (int32_t)blocks, m, tot);
-            GBT_LAUNCHED();
-        } else {
-            GBT_HIP(hipMemcpyAsync(tot, h.data(), (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
-            if (nk) {
-                k_feat_count<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, nk, tot);
+    std::vector<unsigned long long> h(m);  // outlives the copies queued from it
+    uint32_t *out = nullptr;
+    auto group = [&](bool lds) -> gbt_status {
+        const size_t o_cnt = lds ? ((size_t)m * 8 + 255) / 256 * 256 : (size_t)m * 8;
+        const size_t bytes = o_cnt + (lds ? (size_t)blocks * m * 4 : 0);
+        char *w = nullptr;
+        GBT_TRY(dev_alloc(c, bytes, (void **)&w));
+        auto run = [&]() -> gbt_status {
+            unsigned long long *tot = (unsigned long long *)w;
+            uint32_t *cnt = (uint32_t *)(w + o_cnt);
+            const size_t lds_bytes = (size_t)m * 4;
+            std::fill(h.begin(), h.end(), 0ull);
+            if (nk && lds) {
+                k_group_count<<<(unsigned)blocks, kGroupThreads, lds_bytes, c->stream>>>(q->feats, nk, per, m, cnt);
                 GBT_LAUNCHED();
+                k_group_offsets<<<grid_for(m, 64), 64, 0, c->stream>>>(cnt, (int32_t)blocks, m, tot);
+                GBT_LAUNCHED();
+            } else {
+                GBT_HIP(hipMemcpyAsync(tot, h.data(), (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
+                if (nk) {
+                    k_feat_count<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, nk, tot);
+                    GBT_LAUNCHED();
+                }
             }
-        }
-        GBT_HIP(hipMemcpyAsync(h.data(), tot, (size_t)m * 8, hipMemcpyDeviceToHost, c->stream));
-        GBT_HIP(hipStreamSynchronize(c->stream));
-        for (int32_t j = 0; j < m; ++j) {
-            (*seg)[j + 1] = (*seg)[j] + (int64_t)h[j];
-            h[j] = (unsigned long long)(*seg)[j];
-        }
-        uint32_t *out = nullptr;
-        GBT_TRY(room(nk, &out));
-        if (nk == 0) return GBT_OK;
-        GBT_HIP(hipMemcpyAsync(tot, h.data(), (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
-        if (lds)
-            k_group_scatter<<<(unsigned)blocks, kGroupThreads, lds_bytes, c->stream>>>(q->feats, q->keys, nk, per, m,
-                                                                                       cnt, tot, out);
-        else
-            k_feat_scatter<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, q->keys, nk, tot, out);
-        GBT_LAUNCHED();
-        return GBT_OK;
+            GBT_HIP(hipMemcpyAsync(h.data(), tot, (size_t)m * 8, hipMemcpyDeviceToHost, c->stream));
+            GBT_HIP(hipStreamSynchronize(c->stream));
+            seg->assign(m + 1, 0);
+            for (int32_t j = 0; j < m; ++j) {
+                (*seg)[j + 1] = (*seg)[j] + (int64_t)h[j];
+                h[j] = (unsigned long long)(*seg)[j];
+            }
+            GBT_TRY(room(nk, &out));
+            if (nk == 0) return GBT_OK;
+            GBT_HIP(hipMemcpyAsync(tot, h.data(), (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
+            if (lds)
+                k_group_scatter<<<(unsigned)blocks, kGroupThreads, lds_bytes, c->stream>>>(q->feats, q->keys, nk, per,
+                                                                                           m, cnt, tot, out);
+            else
+                k_feat_scatter<<<grid_for(nk, 256), 256, 0, c->stream>>>(q->feats, q->keys, nk, tot, out);
+            GBT_LAUNCHED();
+            return GBT_OK;
+        };
+        const gbt_status s = run();
+        (void)hipStreamSynchronize(c->stream);
+        dev_free(c, w, bytes);
+        return s;
     };
-    const gbt_status s = run();
-    (void)hipStreamSynchronize(c->stream);
-    dev_free(c, w, bytes);
+    const bool lds = m <= kGroupFeats && nk < ((int64_t)1 << 32);
+    gbt_status s = group(lds);
+    if (lds && !out && (s == GBT_E_BUDGET || s == GBT_E_OOM)) s = group(false);
     return s;
 }
 

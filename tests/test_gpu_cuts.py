@@ -165,6 +165,33 @@ def test_csr_matches_oracle(gbt, n, m, density, nan, empty, max_rows, device):
     ctx.close()
 
 
+def test_csr_without_room_for_the_count_tables(gbt):
+    """A budget that holds the pairs, the grouped keys and 8 bytes per
+    feature, but not the grouping's count tables (98 blocks x 2000 features)."""
+    d = csr_rows(20_000, 2000, 0.01, 8)
+    m, nk = 2000, len(d["values"])
+    cuts, _, _, page = oracle_quantize(d, 16)
+
+    def sketched(budget):
+        ctx = gbt.Context(0, budget_bytes=budget)
+        q = gbt.Quantizer(ctx, m, 20_000, max_bin=16, kind=gbt.INPUT_CSR, page_home=gbt.HOME_PINNED_HOST)
+        q.sketch(d)
+        return ctx, q
+
+    ctx, q = sketched(1 << 30)
+    held = ctx.memory()[0]
+    ctx.close()
+    # 98 x 2000 counts are 784 kB; the selection of short segments takes 210 kB
+    ctx, q = sketched(held + 4 * nk + 400_000)
+    q.finalize()
+    q.encode(d)
+    mx = q.end()
+    cp, cv = mx.cuts()
+    assert same_bits(cp, cuts.cut_ptr) and same_bits(cv, cuts.cut_values)
+    assert same_bits(mx.pages(), page)
+    ctx.close()
+
+
 @pytest.mark.parametrize("what", ["equal", "descending", "negative", "large", "indptr"])
 def test_csr_refuses_bad_indices(gbt, what):
     d = csr_rows(600, 30, 0.4, 1)
