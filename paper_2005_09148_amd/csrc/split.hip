@@ -1243,8 +1243,16 @@ __global__ void __launch_bounds__(kPartThreads)
 // 196 against 184 at 32,768; 50 features, depth 8: 244 against 277 at 10,000,
 // 253 against 277 at 16,384, 289 against 275 at 32,768.  The block with most
 // rows sets a level's time, and a built node holds at most half of them, so
-// the limit is twice as high below the root (32,768 rows: 181 and 277 us; four
-// times as high: 209 against 194 us at 65,536).  (A partition by one block of 1024 threads, with the choice, the
+// the row limit is twice as high below the root (32,768 rows: 181 and 277 us; four
+// times as high: 209 against 194 us at 65,536).  Every block reads its node's
+// row ids and pairs again, and a line of the page per row, where a chunk of
+// the other passes reads them once for up to 32 features: R m bounds that
+// work, and m the blocks that do little else than start.  ms for three trees
+// of depth 6 against the chunked passes: 2.1 M cells 0.79 against 0.78 (4096 x
+// 500 of 32 bins) and 0.75 against 0.83 (256 bins), 4.1 M 0.88 against 0.81
+// (8192 x 500, 32 bins), 8.2 M 1.08 against 0.89 (16,384 x 500), 33 M 2.9
+// against 1.5 (16,384 x 2000); 1.0 M cells of 1000 columns 1.00 against 0.87,
+// of 500 columns 0.72 against 0.71 (32 bins).  (A partition by one block of 1024 threads, with the choice, the
 // flags, the scatter and the plan in one kernel, took 21.6 us against 11.6 us
 // for the two kernels over all CUs.)
 template <bool kRows, int kT>
@@ -1362,6 +1370,7 @@ bool small_level_fits(const gbt_matrix *mx, int64_t R, int32_t level)
 {
     // below the root a level's built nodes hold at most R / 2 rows in all
     if (mx->sparse || R <= 0 || R > (level ? 2 * kSmallRows : kSmallRows)) return false;
+    if (mx->m > kSmallCols || R * mx->m > kSmallCells) return false;
     for (int32_t f = 0; f < mx->m; ++f)
         if (mx->bin_ptr_h[f + 1] - mx->bin_ptr_h[f] > 256) return false;
     return true;

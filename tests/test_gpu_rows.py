@@ -62,3 +62,55 @@ def test_small_levels(n, m, max_bin, depth, f, loss):
         outs.append([t.nodes.tobytes() for t in trees] + [margin.cpu().numpy().tobytes(), stats])
     assert outs[0] == outs[1]
     ctx.close()
+
+
+@pytest.mark.parametrize("n,m,max_bin,depth", [(4096, 512, 16, 4), (4097, 512, 16, 4), (300, 512, 256, 3),
+                                               (300, 513, 256, 3)])
+def test_wide_small_trees_match_oracle(n, m, max_bin, depth):
+    """Trees of few rows on both sides of the column and cell limits of the
+    one-kernel levels, bit for bit against the CPU oracle."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import oracle as orc
+    from paper_2005_09148_amd import gbt
+    from tests.gpu_helpers import node_diff, oracle_quantize
+    r = np.random.default_rng(n + m)
+    X = r.normal(size=(n, m)).astype(np.float32)
+    X[r.random(X.shape) < 0.05] = np.nan
+    y = (np.nan_to_num(X[:, 1]) + r.normal(size=n) > 0).astype(np.float32)
+    ctx = gbt.Context(0)
+    trees, margin = gbt.train(ctx, gbt.gbt_quantize(ctx, X, max_bin=max_bin), torch.from_numpy(y).cuda(),
+                              gbt.make_train_params(loss=0, max_depth=depth, eta=0.3), 2, 0.0)
+    _, b, _, _ = oracle_quantize(X, max_bin)
+    want, want_margin = orc.train(b, y, orc.Params(loss=0, max_depth=depth, eta=0.3), 2, 0.0)
+    for g, o in zip(trees, want):
+        assert node_diff(g.nodes, o.nodes) is None
+    assert margin.cpu().numpy().tobytes() == want_margin.tobytes()
+    ctx.close()
+
+
+def test_wide_small_trees_take_no_longer():
+    """16,384 x 2000 rows: the chosen path takes no longer than the chunked
+    passes (one-kernel levels without a bound on the columns took 1.9 times
+    as long; 1.3 allows for the spread of one run)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import time
+    from paper_2005_09148_amd import gbt
+    n, m = 16_384, 2000
+    X = torch.randn(n, m, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    y = (X[:, 0] > 0).float()
+    ctx = gbt.Context(0)
+    mx = gbt.gbt_quantize(ctx, X, max_bin=32)
+    P = gbt.make_train_params(loss=0, max_depth=6, eta=0.1)
+    best = {}
+    for _ in range(6):
+        for kernel in (ctx.HIST_AUTO, ctx.HIST_PLAIN):
+            ctx.set_hist_kernel(kernel)
+            margin = torch.zeros(n, device="cuda")
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            gbt.gbt_train_trees(ctx, mx, y, margin, P, 3)
+            best[kernel] = min(best.get(kernel, 1e9), time.perf_counter() - t)
+    assert best[ctx.HIST_AUTO] < 1.3 * best[ctx.HIST_PLAIN]
+    ctx.close()
