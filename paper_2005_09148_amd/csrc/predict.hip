@@ -211,20 +211,40 @@ bool compact_tree(const gbt_tree &t, int32_t depth, int32_t w, int32_t n_cols, u
 
 }  // namespace
 
-int32_t lds_predict_rows(const gbt_tree *trees, int32_t n_trees, int64_t n_rows, int32_t row_words)
+// Staging a row costs its words whatever the trees read of them, and grows
+// with their square, as wider rows leave fewer waves on a CU to hide it; a
+// step saves about the same whatever the row.  So the walk in LDS pays from
+// steps (of all trees) proportional to the square of the row's loads.  us per
+// call, LDS and global, 1 M raw rows: 40 columns 101 / 121 at 6 steps, 50
+// columns 118 / 73 at 3 and 118 / 125 at 6, 64 columns 182 / 127 at 6 and 208 /
+// 234 at 12 (256 rows a block); 90 columns 467 / 234 at 12 and 560 / 550 at
+// 30, 120 columns 871 / 560 at 30 and 916 / 1021 at 60, 300 columns 7928 /
+// 3079 at 180 and 9621 / 10053 at 600, 480 columns 11424 / 75 at 3 (64 rows a
+// block).  30,000 rows: 120 columns 39 / 33 at 12 and 44 / 52 at 30, 200
+// columns 78 / 81 at 60, 480 columns 331 / 240 at 180 and 465 / 740 at 600; up
+// to 8 steps a walk in global memory ends as soon (26 / 26 at 28 columns and 6
+// steps).  Binned rows take 16-byte loads: 1 M rows of 76 words 114 / 125 at 6
+// steps, of 120 words 281 / 235 at 12 and 301 / 554 at 30.
+int32_t lds_predict_rows(const gbt_tree *trees, int32_t n_trees, int64_t n_rows, int32_t row_words, bool binned)
 {
     int32_t chunk = kChunkWords;
-    int64_t words = 0;
+    int64_t words = 0, steps = 0;
     for (int32_t t = 0; t < n_trees; ++t) {
         if (!trees[t].nodes || trees[t].n_nodes <= 0) return 0;
         const int32_t d = tree_depth(trees[t]);
         if (d > kMaxDepth) return 0;
         chunk = std::max(chunk, tree_words(d));
         words += tree_words(d);
+        steps += d;
     }
     if (n_trees == 0 || words > INT32_MAX / 8) return 0;
-    if (n_rows > kFewRows && lds_bytes(chunk, row_words, 256) <= kLdsRows256) return 256;
-    return lds_bytes(chunk, row_words, 64) <= kLdsRows64 ? 64 : 0;
+    const bool few = n_rows <= kFewRows;
+    const int32_t rows = !few && lds_bytes(chunk, row_words, 256) <= kLdsRows256 ? 256
+                         : lds_bytes(chunk, row_words, 64) <= kLdsRows64         ? 64
+                                                                                 : 0;
+    const int64_t k = (few || rows == 256 ? 400 : 150) * (binned ? 4 : 1);
+    if (k * steps < (int64_t)row_words * row_words || (few && !binned && steps < 8)) return 0;
+    return rows;
 }
 
 gbt_status lds_upload_trees(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, int32_t w, int32_t n_cols,

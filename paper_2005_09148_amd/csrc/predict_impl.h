@@ -14,10 +14,11 @@ struct LdsTrees {
     int32_t chunk_words = 0;          // words of the largest chunk
 };
 
-// Rows per block for the ensemble over n_rows rows of row_words 32-bit words,
-// or 0 when it does not fit the LDS (trees deeper than 11, rows above about
-// 500 words): then the trees are walked in global memory.
-int32_t lds_predict_rows(const gbt_tree *trees, int32_t n_trees, int64_t n_rows, int32_t row_words);
+// Rows per block for the ensemble over n_rows rows of row_words 32-bit words
+// (binned: of symbols), or 0 when it does not fit the LDS (trees deeper than
+// 11, rows above about 500 words) or its steps are too few to pay for staging
+// the rows: then the trees are walked in global memory.
+int32_t lds_predict_rows(const gbt_tree *trees, int32_t n_trees, int64_t n_rows, int32_t row_words, bool binned);
 
 // Compacts the trees and uploads them.  w > 0: splits of binned rows with
 // w-bit symbols; w = 0: splits of raw values.  *ok is false (and nothing is

@@ -2070,11 +2070,11 @@ gbt_status gbt_predict(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, const
     GBT_TRY(set_device(c));
     gbt_node *nodes_d = nullptr;
     int64_t *offs_d = nullptr;
-    // dense rows and trees that fit the LDS are walked there; others (CSR
-    // rows, deep trees, very wide rows) in global memory
+    // dense rows and trees that fit the LDS are walked there when that pays;
+    // others (CSR rows, deep trees, wide rows, few steps) in global memory
     const bool dense = binned ? !binned->sparse : raw->kind == GBT_INPUT_DENSE_F32 && raw->n_cols > 0;
     const int32_t block_rows = dense ? lds_predict_rows(trees, n_trees, binned ? binned->n_rows : raw->n_rows,
-                                                        binned ? binned->row_words : raw->n_cols)
+                                                        binned ? binned->row_words : raw->n_cols, binned != nullptr)
                                      : 0;
     LdsTrees lt;
     bool in_lds = block_rows > 0;

@@ -69,6 +69,19 @@ def walk(gbt, trees, X, base, binned=None):
     (300, 700, [5] * 5, 0), (500, 9, [12, 3], 0), (500, 9, [4] * 9, 3), (35_000, 3, [11, 10, 9], 1)])
 @pytest.mark.parametrize("kind", ["raw", "binned"])
 def test_predict_matches_walk(gbt, n, m, depths, cut, kind):
+    predict_and_walk(gbt, n, m, depths, cut, kind)
+
+
+@pytest.mark.parametrize("n,m,depths", [
+    (400, 90, [4] * 5), (400, 90, [4] * 4 + [5]), (33_000, 40, [3]), (33_000, 40, [4]), (33_000, 5, [0, 1, 2, 0]),
+    (33_000, 90, [6] * 9), (33_000, 90, [5, 6] * 5), (300, 480, [8] * 72), (500, 28, [7]), (500, 28, [4, 4])])
+@pytest.mark.parametrize("kind", ["raw", "binned"])
+def test_predict_around_the_step_rule(gbt, n, m, depths, kind):
+    """Both sides of the line in steps from which rows are staged in LDS."""
+    predict_and_walk(gbt, n, m, depths, 0, kind)
+
+
+def predict_and_walk(gbt, n, m, depths, cut, kind):
     r = np.random.default_rng(n + m)
     X = r.normal(size=(n, m)).astype(np.float32)
     X[r.random(X.shape) < 0.1] = np.nan
@@ -100,4 +113,23 @@ def test_predict_leading_dimension(gbt):
     arr = (gbt.Tree * 5)(*[t.as_struct() for t in trees])
     gbt._check(gbt.lib().gbt_predict(ctx.h, arr, 5, gbt.C.byref(inp), None, 0.0, out.data_ptr()))
     assert out.cpu().numpy().tobytes() == walk(gbt, trees, X, 0.0).tobytes()
+    ctx.close()
+
+
+def test_wide_rows_cost_what_the_trees_read(gbt):
+    """One shallow tree over 1 M x 400 rows reads a few values of each row:
+    less than a copy of the rows (staging whole rows took ten copies)."""
+    import time
+    X = torch.randn(1_000_000, 400, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    trees = ensemble(gbt, [3], 400, 8, 1)
+    ctx = gbt.Context(0)
+    best = {"copy": 1e9, "predict": 1e9}
+    for _ in range(6):
+        for what in best:
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            X.clone() if what == "copy" else gbt.gbt_predict(ctx, trees, 0.0, raw=X)
+            torch.cuda.synchronize()
+            best[what] = min(best[what], time.perf_counter() - t)
+    assert best["predict"] < 3 * best["copy"]
     ctx.close()
