@@ -83,14 +83,13 @@ struct gbt_ctx {
         size_t bytes = 0;
     };
     std::vector<Scratch> scratch;   // reusable workspaces, by slot id
-    // large device blocks: those in use (with their true sizes), and freed
-    // ones kept for the next allocation of about their size (oldest first)
+    // the large device blocks in use, with their true sizes (freed ones are
+    // kept for the context's next allocations)
     struct Block {
         void *p;
         size_t bytes;
     };
-    std::vector<Block> large, spare;
-    size_t spare_bytes = 0;
+    std::vector<Block> large;
     // pinned host memory the kernels write results into (read after a sync)
     void *hio = nullptr;
     void *hio_d = nullptr;
@@ -136,8 +135,6 @@ void timer_collect(gbt_ctx *c, double *ms_per_phase);  // adds, then resets
 
 gbt_status dev_alloc(gbt_ctx *c, size_t bytes, void **p);
 void dev_free(gbt_ctx *c, void *p, size_t bytes);
-// Returns the freed large blocks the context keeps.
-void dev_free_spare(gbt_ctx *c);
 // Grow-only workspace in slot `slot` of the context.
 gbt_status scratch(gbt_ctx *c, int slot, size_t bytes, void **p);
 // Whether scratch(c, slot, bytes) stays within the context's byte budget

@@ -38,28 +38,106 @@ gbt_status set_device(gbt_ctx *c)
 }
 
 // Freed blocks above kSpareMin stay with a context without a byte budget, up
-// to kSpareMax in all, and serve its later allocations of at most their size
-// and at least four fifths of it.  The runtime returns such blocks to the
-// driver, which clears them before it hands them out again: once the card's
-// memory has been through one use, hipMalloc takes about 8 ms per GB (5 ms
-// for 640 MB, 75-100 ms for 2 GB, measured over 500 allocate-and-free pairs;
-// 40 us while unused memory is left), and a 10 M x 50 quantization, which
-// needs 2.7 GB for 5 ms of kernels, took 27 ms.  Blocks up to 64 MB come from
-// the runtime's own pool (12 us).
+// to kSpareMax on a device over all contexts of the process, and serve the
+// context's later allocations of at most their size and at least four fifths
+// of it.  The runtime returns such blocks to the driver, which clears them
+// before it hands them out again: once the card's memory has been through one
+// use, hipMalloc takes about 8 ms per GB (5 ms for 640 MB, 75-100 ms for 2 GB,
+// measured over 500 allocate-and-free pairs; 40 us while unused memory is
+// left), and a 10 M x 50 quantization, which needs 2.7 GB for 5 ms of kernels,
+// took 27 ms.  Blocks up to 64 MB come from the runtime's own pool (12 us).
+// An allocation that fails in any context returns the kept blocks of its
+// device first.
 constexpr size_t kSpareMin = (size_t)64 << 20;
 constexpr size_t kSpareMax = (size_t)4 << 30;
 
-static void drop_spare(gbt_ctx *c, size_t i)
+namespace {
+
+struct Spare {
+    const gbt_ctx *owner;
+    int device;
+    void *p;
+    size_t bytes;
+};
+
+struct SparePool {
+    std::mutex mu;
+    std::vector<Spare> blocks;  // oldest first
+};
+
+SparePool &spare_pool()
 {
-    (void)hipFree(c->spare[i].p);
-    c->spare_bytes -= c->spare[i].bytes;
-    c->spare.erase(c->spare.begin() + (std::ptrdiff_t)i);
+    static SparePool *pool = new SparePool();  // contexts may be destroyed after static objects
+    return *pool;
 }
 
-void dev_free_spare(gbt_ctx *c)
+// Takes the blocks for which take(block) is true out of the pool and frees
+// them (with the lock released: hipFree waits for the device).
+template <typename Take>
+bool drop_spares(Take &&take)
 {
-    while (!c->spare.empty()) drop_spare(c, 0);
+    std::vector<void *> out;
+    {
+        SparePool &pool = spare_pool();
+        std::lock_guard<std::mutex> lock(pool.mu);
+        size_t kept = 0;
+        for (const Spare &b : pool.blocks) {
+            if (take(b))
+                out.push_back(b.p);
+            else
+                pool.blocks[kept++] = b;
+        }
+        pool.blocks.resize(kept);
+    }
+    for (void *p : out) (void)hipFree(p);
+    return !out.empty();
 }
+
+// The context's kept block that serves `bytes` best, out of the pool; p NULL
+// when there is none.
+gbt_ctx::Block take_spare(const gbt_ctx *c, size_t bytes)
+{
+    SparePool &pool = spare_pool();
+    std::lock_guard<std::mutex> lock(pool.mu);
+    size_t best = pool.blocks.size();
+    for (size_t i = 0; i < pool.blocks.size(); ++i) {
+        const Spare &b = pool.blocks[i];
+        if (b.owner == c && b.bytes >= bytes && b.bytes - b.bytes / 5 <= bytes &&
+            (best == pool.blocks.size() || b.bytes < pool.blocks[best].bytes))
+            best = i;
+    }
+    if (best == pool.blocks.size()) return {nullptr, 0};
+    const gbt_ctx::Block out{pool.blocks[best].p, pool.blocks[best].bytes};
+    pool.blocks.erase(pool.blocks.begin() + (std::ptrdiff_t)best);
+    return out;
+}
+
+// Keeps a freed block; the device's oldest ones above kSpareMax in all go.
+void keep_spare(const gbt_ctx *c, const gbt_ctx::Block &b)
+{
+    // as hipFree does: no stream of the block's device uses it any more
+    int device = c->device;
+    (void)hipGetDevice(&device);
+    if (device != c->device) (void)hipSetDevice(c->device);
+    (void)hipDeviceSynchronize();
+    if (device != c->device) (void)hipSetDevice(device);
+    size_t held = 0;
+    {
+        SparePool &pool = spare_pool();
+        std::lock_guard<std::mutex> lock(pool.mu);
+        pool.blocks.push_back({c, c->device, b.p, b.bytes});
+        for (const Spare &s : pool.blocks)
+            if (s.device == c->device) held += s.bytes;
+    }
+    if (held > kSpareMax)
+        drop_spares([&](const Spare &s) {
+            if (s.device != c->device || held <= kSpareMax) return false;
+            held -= s.bytes;
+            return true;
+        });
+}
+
+}  // namespace
 
 gbt_status dev_alloc(gbt_ctx *c, size_t bytes, void **p)
 {
@@ -71,35 +149,23 @@ gbt_status dev_alloc(gbt_ctx *c, size_t bytes, void **p)
                          (unsigned long long)c->used, (unsigned long long)bytes,
                          (unsigned long long)c->budget);
     const bool large = bytes > kSpareMin && !c->budget;
-    if (large) {
-        size_t best = c->spare.size();
-        for (size_t i = 0; i < c->spare.size(); ++i) {
-            const size_t have = c->spare[i].bytes;
-            if (have >= bytes && have - have / 5 <= bytes && (best == c->spare.size() || have < c->spare[best].bytes))
-                best = i;
-        }
-        if (best < c->spare.size()) {
-            c->large.push_back(c->spare[best]);
-            *p = c->spare[best].p;
-            c->spare_bytes -= c->spare[best].bytes;
-            c->spare.erase(c->spare.begin() + (std::ptrdiff_t)best);
-        }
-    }
-    if (!*p) {
-        hipError_t e = hipMalloc(p, bytes);
-        if (e != hipSuccess && !c->spare.empty()) {  // the kept blocks make room
+    gbt_ctx::Block b{nullptr, bytes};
+    if (large) b = take_spare(c, bytes);
+    if (!b.p) {
+        b.bytes = bytes;
+        hipError_t e = hipMalloc(&b.p, bytes);
+        if (e != hipSuccess) {  // the kept blocks make room
             (void)hipGetLastError();
-            dev_free_spare(c);
-            e = hipMalloc(p, bytes);
+            if (drop_spares([&](const Spare &s) { return s.device == c->device; })) e = hipMalloc(&b.p, bytes);
         }
         if (e != hipSuccess) {
-            *p = nullptr;
             (void)hipGetLastError();
             return set_error(GBT_E_OOM, "hipMalloc(%llu) failed: %s", (unsigned long long)bytes,
                              hipGetErrorString(e));
         }
-        if (large) c->large.push_back({*p, bytes});
     }
+    if (large) c->large.push_back(b);
+    *p = b.p;
     c->used += bytes;
     if (c->used > c->peak) c->peak = c->used;
     return GBT_OK;
@@ -115,11 +181,7 @@ void dev_free(gbt_ctx *c, void *p, size_t bytes)
         const gbt_ctx::Block b = c->large[i];
         c->large.erase(c->large.begin() + (std::ptrdiff_t)i);
         if (b.bytes > kSpareMax) break;
-        while (c->spare_bytes + b.bytes > kSpareMax) drop_spare(c, 0);
-        // as hipFree does: no stream uses the block any more
-        (void)hipDeviceSynchronize();
-        c->spare.push_back(b);
-        c->spare_bytes += b.bytes;
+        keep_spare(c, b);
         return;
     }
     (void)hipFree(p);
@@ -343,7 +405,7 @@ gbt_status gbt_ctx_destroy(gbt_ctx *c)
     (void)hipStreamSynchronize(c->stream);
     (void)hipStreamSynchronize(c->side);
     for (auto &s : c->scratch) dev_free(c, s.p, s.bytes);
-    dev_free_spare(c);
+    drop_spares([&](const Spare &s) { return s.owner == c; });
     if (c->hio) (void)hipHostFree(c->hio);
     if (c->tres) (void)hipHostFree(c->tres);
     for (auto e : c->tres_ev) (void)hipEventDestroy(e);

@@ -134,6 +134,40 @@ def test_kept_blocks(gbt):
     plain.close()
 
 
+def free_bytes():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def test_kept_blocks_make_room_for_other_contexts(gbt):
+    """An allocation that fails in one context returns the blocks that the
+    others keep."""
+    X = torch.randn(4_000_000, 28, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda")
+    ctx, other = gbt.Context(0), gbt.Context(0, budget_bytes=1 << 50)
+    gbt.gbt_quantize(ctx, X).free()
+    kept = free_bytes()
+    with pytest.raises(gbt.GbtError) as err:  # 1 TiB of keys: more than the card holds
+        gbt.Quantizer(other, 64, 1 << 32, sketch_max_rows=1 << 40)
+    assert err.value.code == gbt.GBT_E_OOM
+    assert free_bytes() - kept >= 4_000_000 * 28 * 4
+    cuts = gbt.gbt_quantize(ctx, X).cuts()[1]  # the context goes on
+    assert same_bits(cuts, gbt.gbt_quantize(other, X).cuts()[1])
+    ctx.close()
+    other.close()
+
+
+def test_kept_blocks_are_bounded_over_contexts(gbt):
+    X = torch.randn(12_000_000, 28, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda")
+    before = free_bytes()
+    ctxs = [gbt.Context(0) for _ in range(4)]
+    for ctx in ctxs:  # 1.3 GB of keys and more each
+        gbt.gbt_quantize(ctx, X).free()
+    assert before - free_bytes() < (4 << 30) + (256 << 20)
+    for ctx in ctxs:
+        ctx.close()
+    assert before - free_bytes() < 256 << 20
+
+
 def csr_rows(n, m, density, seed, nan=0.0, empty=0.0):
     r = np.random.default_rng(seed)
     lens = np.minimum(r.binomial(m, density, n), m)
