@@ -279,16 +279,33 @@ class Context:
         h = C.c_void_p()
         _check(_lib.gbt_ctx_create(device, budget_bytes, s.cuda_stream, C.byref(h)))
         self.h = h
-        # library objects made on this context, released before it
-        self._owned = weakref.WeakSet()
+        self._track()
 
-    def _own(self, obj):
+    def _track(self):
+        # library objects made on this context, released before it: the live
+        # Python objects, and every handle not yet freed.  When the garbage
+        # collector takes a cycle that holds the context and its objects, it
+        # clears the weak references first and may finalize the context
+        # before them; the handles are known all the same, and an object
+        # finalized later finds its handle gone.
+        self._owned = weakref.WeakSet()
+        self._handles = {}
+
+    def _own(self, obj, free):
         self._owned.add(obj)
+        self._handles[id(obj)] = (free, obj.h)
+
+    def _disown(self, obj) -> bool:
+        """Whether obj's handle was still to be freed; the caller frees it."""
+        return self._handles.pop(id(obj), None) is not None
 
     def close(self):
         if self.h:
             for obj in list(self._owned):
                 obj.free()
+            while self._handles:
+                free, h = self._handles.popitem()[1]
+                free(h)
             _lib.gbt_ctx_destroy(self.h)
             self.h = None
 
@@ -387,12 +404,12 @@ class Matrix:
         self.ctx = ctx
         self.h = handle
         self._info = None
-        ctx._own(self)
+        ctx._own(self, _lib.gbt_matrix_free)
 
     def free(self):
-        if self.h:
+        if self.h and self.ctx._disown(self):
             _lib.gbt_matrix_free(self.h)
-            self.h = None
+        self.h = None
 
     def __del__(self):
         try:
@@ -460,7 +477,7 @@ class Quantizer:
         _check(_lib.gbt_quantize_begin(ctx.h, C.byref(qp), n_cols, n_rows_total, kind,
                                        C.byref(h)))
         self.h = h
-        ctx._own(self)
+        ctx._own(self, _lib.gbt_quantizer_free)
 
     def sketch(self, X):
         """One batch (Alg. 3): dense X, or CSR as a dict kind='csr'."""
@@ -485,13 +502,14 @@ class Quantizer:
     def end(self) -> Matrix:
         m = C.c_void_p()
         _check(_lib.gbt_quantize_end(self.h, C.byref(m)))
+        self.ctx._disown(self)
         self.h = None
         return Matrix(self.ctx, m)
 
     def free(self):
-        if getattr(self, "h", None):
+        if getattr(self, "h", None) and self.ctx._disown(self):
             _lib.gbt_quantizer_free(self.h)
-            self.h = None
+        self.h = None
 
     def __del__(self):
         try:

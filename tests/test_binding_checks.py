@@ -88,3 +88,58 @@ def test_build_hist_checks(gbt):
         gbt.gbt_build_hist(CTX, FakeMatrix(), page, q[: N // 2], None, [(0, 0, N)], hist=hist)
     with pytest.raises(ValueError, match="must be on cuda"):
         gbt.gbt_build_hist(CTX, FakeMatrix(), page, q, None, [(0, 0, N)], hist=hist)
+
+
+class Recorder:
+    """Stands in for the library: which handle is freed when."""
+
+    def __init__(self):
+        self.freed = []
+
+    def __getattr__(self, name):
+        def call(h, *_):
+            self.freed.append((name, h))
+            return 0
+        return call
+
+
+def owned_objects(gbt):
+    ctx = gbt.Context.__new__(gbt.Context)
+    ctx.h = "ctx"
+    ctx._track()
+    q = gbt.Quantizer.__new__(gbt.Quantizer)
+    q.ctx, q.h = ctx, "q"
+    ctx._own(q, gbt._lib.gbt_quantizer_free)
+    return ctx, q, gbt.Matrix(ctx, "m")
+
+
+@pytest.mark.parametrize("how", ["cycle", "close", "objects first", "context dropped"])
+def test_objects_are_freed_before_their_context(gbt, monkeypatch, how):
+    """A library object freed after its context reads freed memory: the order
+    holds also when a cycle (here a list, in earnest a traceback's frames)
+    leaves it to the garbage collector."""
+    import gc
+    rec = Recorder()
+    monkeypatch.setattr(gbt, "_lib", rec)
+    gc.collect()
+    ctx, q, m = owned_objects(gbt)
+    if how == "cycle":
+        cycle = [ctx, q, m]
+        cycle.append(cycle)
+        del cycle
+    elif how == "close":
+        ctx.close()
+        assert q.h is None and m.h is None
+        m.free()
+    elif how == "objects first":
+        m.free()
+        m.free()
+        del q
+        ctx.close()
+    else:
+        del ctx, q
+        m.free()
+    ctx = q = m = None
+    gc.collect()
+    assert sorted(rec.freed) == [("gbt_ctx_destroy", "ctx"), ("gbt_matrix_free", "m"), ("gbt_quantizer_free", "q")]
+    assert rec.freed[-1][0] == "gbt_ctx_destroy"
