@@ -35,7 +35,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 METRIC = "histogram row-feature updates/sec (G/s), sec/tree, achieved HBM GB/s on 1 MI355X"
 # the dense histogram kernels, by the hist_kernel field of the tree stats
-HIST_KERNELS = {1: "k_hist_dense", 2: "k_hist_rot"}
+HIST_KERNELS = {1: "k_hist_dense", 2: "k_hist_rot", 3: "k_small_level"}
 # sources of the histogram kernel: stored counter traffic is reported only
 # while these are unchanged
 HIST_SOURCES = ["hist.hip", "hist_impl.h", "common.h"]

@@ -194,14 +194,17 @@ typedef struct {
     int64_t hist_updates;   /* non-null (row, feature) updates performed */
     int64_t hist_bytes;     /* algorithmic bytes of the histogram kernels */
     /* kernel time per phase, from HIP events on the context stream (timing on) */
-    double ms_hist;         /* histogram-building kernel */
+    double ms_hist;         /* histogram-building kernel (levels of few rows have one kernel that
+                               also subtracts and evaluates: all of it is counted here) */
     double ms_hist_aux;     /* histogram zeroing and sibling subtraction */
     double ms_sample;       /* gradients, sampling, compaction, fixed point */
     double ms_split;        /* split evaluation and partitioning */
     double ms_margin;       /* leaves and the margin update */
     double ms_total;        /* wall time of the call */
     double h2d_bytes;       /* bytes streamed from pinned-host or disk pages */
-    int32_t hist_kernel;    /* GBT_HIST_PLAIN or GBT_HIST_ROTATED (dense), 0 sparse */
+    int32_t hist_kernel;    /* the root pass's: GBT_HIST_PLAIN or GBT_HIST_ROTATED (dense),
+                               GBT_HIST_LEVEL (dense, few rows: the one kernel of a level),
+                               0 sparse */
     int32_t hist_cols;      /* bytes per symbol (1 or 2) of the partition's column copy of
                                the training page when the root histogram pass also wrote it
                                (counted in hist_bytes); 0: a kernel of its own did or none
@@ -255,7 +258,8 @@ gbt_status gbt_ctx_destroy(gbt_ctx *ctx);
  * context on the device fails and when their context is destroyed. */
 gbt_status gbt_ctx_memory(gbt_ctx *ctx, uint64_t *used_bytes, uint64_t *peak_bytes);
 /* HIP events on the context stream (gbt_tree_stats.ms_*): 0 off, 1 around
- * the histogram-building kernel only, 2 around every phase. */
+ * the histogram-building kernel only (with the evaluation where a level of
+ * few rows has one kernel for both), 2 around every phase. */
 gbt_status gbt_ctx_set_timing(gbt_ctx *ctx, int32_t level);
 /* Which dense histogram kernel the context uses (results are identical):
  * GBT_HIST_AUTO chooses by pass size, GBT_HIST_PLAIN forces one lane per row
@@ -265,6 +269,7 @@ gbt_status gbt_ctx_set_timing(gbt_ctx *ctx, int32_t level);
 #define GBT_HIST_AUTO 0
 #define GBT_HIST_PLAIN 1
 #define GBT_HIST_ROTATED 2
+#define GBT_HIST_LEVEL 3 /* in gbt_tree_stats only: GBT_HIST_AUTO chooses it */
 gbt_status gbt_ctx_set_hist_kernel(gbt_ctx *ctx, int32_t choice);
 
 /* How the compaction of Alg. 7 (Sec. 3.4) reads pages held in pinned host

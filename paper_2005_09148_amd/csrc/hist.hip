@@ -13,7 +13,6 @@
 // share its L2 for the gradient pairs and row ids.
 #include "hist_impl.h"
 
-#include <hip/hip_ext.h>
 
 #include <algorithm>
 #include <cstring>
@@ -836,21 +835,6 @@ static gbt_status static_scratch(int device, HistWorkspace *ws)
     ws->bytes = kStaticScratchBytes;
     return GBT_OK;
 }
-
-// A histogram kernel launch on the context stream; with a timer mark the
-// launch fills the mark's events with its own start and end (the kernel's
-// time, without the dispatch around it).
-#define GBT_HIST_LAUNCH(KFN, GRID, BLOCK, LDS, ...)                                                       \
-    do {                                                                                                 \
-        if (mark >= 0) {                                                                                 \
-            hipEvent_t ev_a, ev_b;                                                                       \
-            timer_events(c, mark, &ev_a, &ev_b);                                                         \
-            hipExtLaunchKernelGGL(KFN, dim3(GRID), dim3(BLOCK), (uint32_t)(LDS), c->stream, ev_a, ev_b, 0u, \
-                                  __VA_ARGS__);                                                          \
-        } else {                                                                                         \
-            KFN<<<GRID, BLOCK, LDS, c->stream>>>(__VA_ARGS__);                                           \
-        }                                                                                                \
-    } while (0)
 
 gbt_status hist_launch_device(gbt_ctx *c, const gbt_matrix *mx, const uint32_t *page, const int64_t *q,
                               const int32_t *rows, const HistLaunch &hl, const int64_t *parent_hist,

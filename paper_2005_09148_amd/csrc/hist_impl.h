@@ -2,11 +2,27 @@
 // by the tree driver, which plans the levels below the root on the device.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <vector>
 
 #include "common.h"
 
 namespace gbt {
+
+// A histogram kernel launch on the context stream; with a timer mark the
+// launch fills the mark's events with its own start and end (the kernel's
+// time, without the dispatch around it).
+#define GBT_HIST_LAUNCH(KFN, GRID, BLOCK, LDS, ...)                                                       \
+    do {                                                                                                 \
+        if (mark >= 0) {                                                                                 \
+            hipEvent_t ev_a, ev_b;                                                                       \
+            timer_events(c, mark, &ev_a, &ev_b);                                                         \
+            hipExtLaunchKernelGGL(KFN, dim3(GRID), dim3(BLOCK), (uint32_t)(LDS), c->stream, ev_a, ev_b, 0u, \
+                                  __VA_ARGS__);                                                          \
+        } else {                                                                                         \
+            KFN<<<GRID, BLOCK, LDS, c->stream>>>(__VA_ARGS__);                                           \
+        }                                                                                                \
+    } while (0)
 
 struct HistWork {
     int64_t begin, end;  // rows[begin, end) of one node

@@ -1382,16 +1382,14 @@ gbt_status small_level(gbt_ctx *c, const gbt_matrix *mx, const uint32_t *page, c
                        unsigned long long *upd, const ColCopy &cols)
 {
     const dim3 grid((unsigned)mx->m, (unsigned)max_red);
-    const int mark = timer_begin(c, kPhHist);
+    const int mark = timer_begin_launch(c, kPhHist);
     // two blocks of 1024 threads per CU, or more blocks of 256
     const int threads = (int64_t)mx->m * max_red <= 2 * kCUs ? 1024 : 256;
     auto kfn = threads == 1024 ? (rows ? k_small_level<true, 1024> : k_small_level<false, 1024>)
                                : (rows ? k_small_level<true, 256> : k_small_level<false, 256>);
-    kfn<<<grid, threads, 0, c->stream>>>(page, geo_of(mx), (const longlong2 *)q, rows, work, red, n_red_d,
-                                         (const longlong2 *)parent, (longlong2 *)hist, mx->total_bins, ev, ep, cand,
-                                         upd, cols);
+    GBT_HIST_LAUNCH(kfn, grid, threads, 0, page, geo_of(mx), (const longlong2 *)q, rows, work, red, n_red_d,
+                    (const longlong2 *)parent, (longlong2 *)hist, mx->total_bins, ev, ep, cand, upd, cols);
     GBT_LAUNCHED();
-    timer_end(c, mark);
     return GBT_OK;
 }
 

@@ -1374,7 +1374,10 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
     pt->stats = want_stats;
     pt->key_lambda = sample_lambda(sp);
     pt->hist_launches = hist_launches;
-    pt->hist_kind = hp.kind == kHistRot ? GBT_HIST_ROTATED : (hp.kind == kHistDense ? GBT_HIST_PLAIN : 0);
+    pt->hist_kind = small_at(0)              ? GBT_HIST_LEVEL
+                    : hp.kind == kHistRot   ? GBT_HIST_ROTATED
+                    : hp.kind == kHistDense ? GBT_HIST_PLAIN
+                                            : 0;
     pt->cols_bytes = cols_root.bytes;
     pt->hist_bytes_fixed = (D > 0 ? R : 0) * (wbytes + 16) + root_built * mx->total_bins * 16 +
                            (int64_t)cols_root.bytes * mx->m * R;

@@ -325,6 +325,7 @@ class Context:
         _check(_lib.gbt_ctx_set_timing(self.h, int(level)))
 
     HIST_AUTO, HIST_PLAIN, HIST_ROTATED = 0, 1, 2
+    HIST_LEVEL = 3  # in the tree stats only
 
     def set_hist_kernel(self, choice: int):
         """Dense histogram kernel: HIST_AUTO (by pass size), HIST_PLAIN or

@@ -114,3 +114,23 @@ def test_wide_small_trees_take_no_longer():
             best[kernel] = min(best.get(kernel, 1e9), time.perf_counter() - t)
     assert best[ctx.HIST_AUTO] < 1.3 * best[ctx.HIST_PLAIN]
     ctx.close()
+
+
+@pytest.mark.parametrize("n,forced,kind", [(10_000, False, 3), (10_000, True, 1), (20_000, False, 1)])
+def test_stats_name_the_root_kernel(n, forced, kind):
+    """The stats of a tree whose root level is one kernel (HIST_LEVEL), of
+    the forced plain kernel and of a tree above the root's row limit."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2005_09148_amd import gbt
+    X = torch.randn(n, 20, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    ctx = gbt.Context(0)
+    ctx.set_timing(1)
+    if forced:
+        ctx.set_hist_kernel(ctx.HIST_PLAIN)
+    mx = gbt.gbt_quantize(ctx, X)
+    st = gbt.gbt_train_tree(ctx, mx, (X[:, 0] > 0).float(), torch.zeros(n, device="cuda"),
+                            gbt.make_train_params(loss=0, max_depth=5)).stats
+    assert st.hist_kernel == kind and st.hist_launches == 5
+    assert 0 < st.ms_hist < st.ms_total and st.ms_split == 0
+    ctx.close()
