@@ -371,9 +371,10 @@ __device__ inline uint32_t sparse_symbol(const uint32_t *__restrict__ row, int32
 // Whole work items are dealt over the XCDs, so the groups of one item share
 // its L2 for the rows; with contiguous runs of (item, group) pairs per XCD
 // the passes below the root took 82 us on average (2 M rows x 2000 features,
-// depth 10) and up to 226 us, now 71 us and at most 115 us.  The row-id and
-// slot-range chain does not bound a pass: with all of it requested a row
-// ahead it took the same time.
+// depth 10) and up to 226 us, now 71 us and at most 115 us.  A pass of fewer
+// items than XCDs deals the pairs instead, as whole items would leave XCDs
+// idle.  The row-id and slot-range chain does not bound a pass: with all of
+// it requested a row ahead it took the same time.
 template <bool kRows>
 __global__ void __launch_bounds__(kSparseThreads)
     k_hist_sparse(const uint32_t *__restrict__ page, int32_t row_words, int32_t w, uint32_t mask,
@@ -384,12 +385,24 @@ __global__ void __launch_bounds__(kSparseThreads)
                   const uint8_t *__restrict__ slot_tbl, int32_t tbl_stride)
 {
     extern __shared__ unsigned long long lds[];
-    const int32_t lb = (int32_t)(blockIdx.x / kXcds), item = lb / n_groups * kXcds + (int32_t)(blockIdx.x % kXcds);
-    const int32_t gi = lb % n_groups;
-    if (item >= max_work) return;
-    const HistWork wk = work[item];
-    const HistGroup gr = groups[gi];
-    if (n_work_d && item >= *n_work_d) return;
+    const int32_t lb = (int32_t)(blockIdx.x / kXcds);
+    const int32_t item = lb / n_groups * kXcds + (int32_t)(blockIdx.x % kXcds);
+    int32_t gi = lb % n_groups;
+    // the records of a pass of at least kXcds items are requested with the
+    // count, not after it (item < max_work <= the list's room)
+    HistWork wk = work[min(item, max_work - 1)];
+    HistGroup gr = groups[gi];
+    const int32_t items = n_work_d ? *n_work_d : max_work;
+    if (items < kXcds) {
+        const uint32_t active = (uint32_t)(items * n_groups);
+        if (blockIdx.x >= active) return;
+        const uint32_t L = xcd_remap(blockIdx.x, active);
+        wk = work[L / n_groups];
+        gi = (int32_t)(L % n_groups);
+        gr = groups[gi];
+    } else if (item >= items) {
+        return;
+    }
     const int32_t nb = gr.b1 - gr.b0;
     unsigned long long *sg = lds, *sh = lds + nb;
     lds_zero(sg, sh, nb);

@@ -134,3 +134,30 @@ def test_stats_name_the_root_kernel(n, forced, kind):
     assert st.hist_kernel == kind and st.hist_launches == 5
     assert 0 < st.ms_hist < st.ms_total and st.ms_split == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("n,m,density", [(1500, 3000, 0.01), (14_000, 1500, 0.01), (40_000, 600, 0.02)])
+def test_sparse_passes_of_few_items_match_oracle(n, m, density):
+    """Sparse passes with fewer work items than XCDs (2048 rows each), with
+    more, and of both in one tree, over several feature groups."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import oracle as orc
+    from paper_2005_09148_amd import gbt
+    from tests.gpu_helpers import node_diff, oracle_quantize
+    r = np.random.default_rng(n + m)
+    lens = r.binomial(m, density, n)
+    d = {"kind": "csr", "indptr": np.concatenate([[0], np.cumsum(lens)]).astype(np.int64),
+         "indices": np.concatenate([np.sort(r.choice(m, k, replace=False)) for k in lens]).astype(np.int32), "m": m}
+    d["values"] = np.exp(r.normal(size=len(d["indices"]))).astype(np.float32)
+    y = (r.random(n) < 0.5).astype(np.float32)
+    ctx = gbt.Context(0)
+    mx = gbt.gbt_quantize(ctx, d, max_bin=32)
+    trees, margin = gbt.train(ctx, mx, torch.from_numpy(y).cuda(), gbt.make_train_params(loss=0, max_depth=4, eta=0.3),
+                              2, 0.0)
+    _, b, _, _ = oracle_quantize(d, 32)
+    want, want_margin = orc.train(b, y, orc.Params(loss=0, max_depth=4, eta=0.3), 2, 0.0)
+    for g, o in zip(trees, want):
+        assert node_diff(g.nodes, o.nodes) is None
+    assert margin.cpu().numpy().tobytes() == want_margin.tobytes()
+    ctx.close()
