@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(kCsrRows)
         __syncthreads();  // the counts of the step before are read
         if (lane == 0) wsum[wid] = __popcll(mask);
         __syncthreads();
-        unsigned long long o = at + __popcll(mask & ((1ull << lane) - 1ull));
+        unsigned long long o = at + lanes_below(mask);
         for (int w = 0; w < kCsrRows / 64; ++w) {
             if (w < wid) o += wsum[w];
             at += wsum[w];

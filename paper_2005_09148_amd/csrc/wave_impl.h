@@ -24,6 +24,13 @@ namespace gbt {
 constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
 constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
 
+// Set bits of a wave mask below this lane (the hardware's masked bit count;
+// no 64-bit shift by the lane).
+__device__ inline int lanes_below(uint64_t mask)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
 template <int kCtrl, int kRowMask>
 __device__ inline uint32_t dpp32(uint32_t old, uint32_t v)
 {
