@@ -72,18 +72,47 @@ def test_pages_match_oracle(gbt, n, m, max_bin, ld, page_rows):
     ctx.close()
 
 
+def sample_places(n, feature):
+    """Places of the selection's sample of a segment of n keys (cuts.hip):
+    one scrambled place in each of 16384 equal strata."""
+    i = np.arange(16384, dtype=np.uint64)
+    lo, hi = i * n // 16384, (i + 1) * n // 16384
+    h = (i * 0x9e3779b9 + feature) & 0xffffffff
+    for shift, mul in ((16, 0x7feb352d), (15, 0x846ca68b), (16, 1)):
+        h = (h ^ (h >> np.uint64(shift))) * np.uint64(mul) & np.uint64(0xffffffff)
+    return (lo + h % (hi - lo)).astype(np.int64)
+
+
+def rank_buckets(x, max_bin):
+    """Keys and ranks of the selection's buckets that hold a rank, for a
+    column x of positive values of which none is frequent in its sample."""
+    q = np.sort(x[sample_places(len(x), 0)])[np.arange(1, 4096) * 4]
+    assert (np.diff(q) > 0).all()
+    v = np.sort(x)
+    ranks = (np.arange(1, max_bin, dtype=np.int64) * len(x) + max_bin - 1) // max_bin - 1
+    ends = np.concatenate([np.searchsorted(v, q, side="right"), [len(x)]])
+    holds = np.searchsorted(ends, np.concatenate([ranks, [len(x) - 1]]), side="right")
+    at, per = np.unique(holds, return_counts=True)
+    return np.diff(np.concatenate([[0], ends]))[at], per, np.unique(v[ranks])
+
+
 def test_uneven_buckets(gbt):
-    """A run of close keys that the sample hardly meets: its bucket holds more
-    keys than one block sorts, and ranks fall into it."""
-    n = 4_000_000
-    x = torch.zeros(n, 1, device="cuda")
-    g = torch.Generator(device="cuda").manual_seed(3)
-    x[:, 0] = torch.randint(0, 30_000_000, (n,), generator=g, device="cuda").float()
+    """Every size of bucket: 20,000 close keys at places that are not in the
+    sample share a bucket with several ranks (searched digit by digit: more
+    than one block sorts), others hold up to 1024 keys and up to 4096."""
+    n, bins = 4_000_000, 1024
+    r = np.random.default_rng(3)
+    x = r.integers(1, 16_000_000, n)
+    x[(x >= 9_000_000) & (x < 9_040_000)] -= 5_000_000
+    free = np.setdiff1d(np.arange(n), sample_places(n, 0))
+    x[r.choice(free, 20_000, replace=False)] = 9_010_000 + r.permutation(20_000)
+    x = x.astype(np.float32)
+    keys, ranks, cuts = rank_buckets(x, bins)
+    assert (keys <= 1024).any() and ((keys > 1024) & (keys <= 4096)).any()
+    assert (ranks[keys > 4096] > 2).any()
     ctx = gbt.Context(0)
-    mx = gbt.gbt_quantize(ctx, x, max_bin=1024)
-    v = np.sort(x.cpu().numpy()[:, 0])
-    c = np.unique(v[(np.arange(1, 1024) * n + 1023) // 1024 - 1])
-    assert same_bits(mx.cuts()[1], c[c < v[-1]])
+    mx = gbt.gbt_quantize(ctx, torch.from_numpy(x[:, None]).cuda(), max_bin=bins)
+    assert same_bits(mx.cuts()[1], cuts[cuts < x.max()])
     ctx.close()
 
 
