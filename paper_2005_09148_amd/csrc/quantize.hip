@@ -124,6 +124,13 @@ __global__ void __launch_bounds__(kSkThreads)
 // per row, reading its 20 entries alone, took 2.5 ms.
 constexpr int kCsrRows = 256, kCsrTile = 8192;
 
+// Rows per block: kCsrRows, fewer when so many rows of m entries would pass
+// 2^30 (the block counts its entries in 32 bits).
+int32_t csr_block_rows(int32_t m)
+{
+    return (int32_t)std::min<int64_t>(kCsrRows, std::max<int64_t>(1, ((int64_t)1 << 30) / m));
+}
+
 // Row whose entries [ptr[r], ptr[r + 1]) hold entry e (ptr[0] <= e < ptr[n]).
 __device__ inline int32_t row_of_entry(const int32_t *ptr, int32_t n, int32_t e)
 {
@@ -139,7 +146,8 @@ __device__ inline int32_t row_of_entry(const int32_t *ptr, int32_t n, int32_t e)
 }
 
 // The block's rows [r0, r0 + nr) as entry offsets from the first one's start
-// (*e0); false when they descend or leave [0, nnz].
+// (*e0); false when they descend, leave [0, nnz] or span 2^31 - 2 kCsrTile or
+// more entries (so that the steps past their end stay in 32 bits).
 __device__ inline bool load_row_ptr(const int64_t *__restrict__ indptr, int64_t base, int64_t r0, int32_t nr,
                                     int64_t nnz, int32_t *ptr, int64_t *e0, int32_t *s_bad)
 {
@@ -150,7 +158,7 @@ __device__ inline bool load_row_ptr(const int64_t *__restrict__ indptr, int64_t 
     for (int32_t i = threadIdx.x; i <= nr; i += kCsrRows) {
         const int64_t a = indptr[r0 + i] - base;
         if (i > 0 && a < indptr[r0 + i - 1] - base) bad = true;
-        if (a > nnz || a - first > INT32_MAX) bad = true;
+        if (a > nnz || a - first >= INT32_MAX - 2 * kCsrTile) bad = true;
         ptr[i] = (int32_t)(a - first);
     }
     if (bad) *s_bad = 1;
@@ -161,16 +169,16 @@ __device__ inline bool load_row_ptr(const int64_t *__restrict__ indptr, int64_t 
 
 __global__ void __launch_bounds__(kCsrRows)
     k_csr_sketch(const int64_t *__restrict__ indptr, const int32_t *__restrict__ idx, const float *__restrict__ val,
-                 int64_t rows, int64_t nnz, int32_t m, int64_t row0, int64_t stride, uint32_t *__restrict__ keys,
-                 int32_t *__restrict__ feats, unsigned long long *__restrict__ st)
+                 int64_t rows, int32_t block_rows, int64_t nnz, int32_t m, int64_t row0, int64_t stride,
+                 uint32_t *__restrict__ keys, int32_t *__restrict__ feats, unsigned long long *__restrict__ st)
 {
     __shared__ int32_t ptr[kCsrRows + 1], nan[kCsrRows];
     __shared__ uint32_t start[kCsrTile / 32];
     __shared__ int32_t wsum[kCsrRows / 64];
     __shared__ int32_t s_bad, s_nan, s_max;
     __shared__ unsigned long long s_at;
-    const int64_t r0 = (int64_t)blockIdx.x * kCsrRows;
-    const int32_t nr = (int32_t)(rows - r0 < kCsrRows ? rows - r0 : kCsrRows);
+    const int64_t r0 = (int64_t)blockIdx.x * block_rows;
+    const int32_t nr = (int32_t)(rows - r0 < block_rows ? rows - r0 : block_rows);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     int64_t e0;
     if (!load_row_ptr(indptr, indptr[0], r0, nr, nnz, ptr, &e0, &s_bad)) {
@@ -508,7 +516,7 @@ __global__ void __launch_bounds__(kEncRows)
 // ms with a lane per row throughout.
 __global__ void __launch_bounds__(kCsrRows)
     k_encode_csr(const int64_t *__restrict__ indptr, const int32_t *__restrict__ idx, const float *__restrict__ val,
-                 int64_t rows, int64_t nnz, int32_t m, const int64_t *__restrict__ entry0,
+                 int64_t rows, int32_t block_rows, int64_t nnz, int32_t m, const int64_t *__restrict__ entry0,
                  const int32_t *__restrict__ cut_ptr, const float *__restrict__ cut_values,
                  const int32_t *__restrict__ bin_ptr, int32_t w, int32_t stride, int32_t row_words, uint32_t null_sym,
                  uint32_t *__restrict__ out, unsigned long long *__restrict__ st)
@@ -517,8 +525,8 @@ __global__ void __launch_bounds__(kCsrRows)
     __shared__ uint32_t sym[kCsrTile];
     __shared__ int32_t s_bad;
     constexpr uint32_t kSkip = 0xffffffffu;  // a missing value
-    const int64_t r0 = (int64_t)blockIdx.x * kCsrRows;
-    const int32_t nr = (int32_t)(rows - r0 < kCsrRows ? rows - r0 : kCsrRows);
+    const int64_t r0 = (int64_t)blockIdx.x * block_rows;
+    const int32_t nr = (int32_t)(rows - r0 < block_rows ? rows - r0 : block_rows);
     int64_t e0;
     if (!load_row_ptr(indptr, entry0[0], r0, nr, nnz, ptr, &e0, &s_bad)) {
         if (threadIdx.x == 0) atomicOr(&st[kStBadIndex], 1ull);
@@ -941,8 +949,9 @@ gbt_status gbt_quantize_sketch_batch(gbt_quantizer *q, const gbt_input *batch)
                 q->keys_bytes = q->feats_bytes = (size_t)cap * 4;
                 q->keys_cap = cap;
             }
-            k_csr_sketch<<<grid_for(b.rows, kCsrRows), kCsrRows, 0, c->stream>>>(
-                b.indptr, b.indices, b.values, b.rows, b.nnz, q->m, q->sketched_rows, q->stride, q->keys,
+            const int32_t block_rows = csr_block_rows(q->m);
+            k_csr_sketch<<<grid_for(b.rows, block_rows), kCsrRows, 0, c->stream>>>(
+                b.indptr, b.indices, b.values, b.rows, block_rows, b.nnz, q->m, q->sketched_rows, q->stride, q->keys,
                 q->feats, q->st);
             GBT_LAUNCHED();
             if (q->ms) GBT_TRY(csr_merge_batch(q));
@@ -1313,6 +1322,7 @@ gbt_status gbt_quantize_encode_batch(gbt_quantizer *q, const gbt_input *batch)
     GBT_CHECK(q->encoded_rows + b.rows <= q->n_total, "more rows than announced");
     if (b.rows == 0) return GBT_OK;
     // rows [r, r + n) of the batch, encoded at `out`
+    const int32_t block_rows = csr_block_rows(mx->m);
     int32_t lg = 0, cols = kEncCols;
     if (!mx->sparse) {
         int32_t most = 0;
@@ -1327,9 +1337,9 @@ gbt_status gbt_quantize_encode_batch(gbt_quantizer *q, const gbt_input *batch)
                 b.values + r * b.ld, n, mx->m, b.ld, mx->cut_ptr_d, mx->cut_values_d, mx->w, mx->row_words,
                 mx->null_sym, lg, cols, out);
         else
-            k_encode_csr<<<grid_for(n, kCsrRows), kCsrRows, 0, c->stream>>>(
-                b.indptr + r, b.indices, b.values, n, b.nnz, mx->m, b.indptr, mx->cut_ptr_d, mx->cut_values_d, mx->bin_ptr_d, mx->w,
-                mx->stride, mx->row_words, mx->null_sym, out, q->st);
+            k_encode_csr<<<grid_for(n, block_rows), kCsrRows, 0, c->stream>>>(
+                b.indptr + r, b.indices, b.values, n, block_rows, b.nnz, mx->m, b.indptr, mx->cut_ptr_d,
+                mx->cut_values_d, mx->bin_ptr_d, mx->w, mx->stride, mx->row_words, mx->null_sym, out, q->st);
         GBT_LAUNCHED();
         return GBT_OK;
     };

@@ -228,6 +228,25 @@ def test_csr_matches_oracle(gbt, n, m, density, nan, empty, max_rows, device):
     ctx.close()
 
 
+def test_csr_blocks_of_fewer_rows(gbt):
+    """Above 2^22 columns a block takes fewer than 256 rows (here 107)."""
+    n, m = 700, 10_000_000
+    r = np.random.default_rng(6)
+    lens = r.integers(0, 60, n)
+    d = {"kind": "csr", "indptr": np.concatenate([[0], np.cumsum(lens)]).astype(np.int64), "m": m,
+         "indices": np.concatenate([np.sort(r.choice(10_000_000 // 50, k, replace=False) * 50) for k in lens])}
+    d["indices"] = d["indices"].astype(np.int32)
+    d["values"] = r.normal(size=len(d["indices"])).astype(np.float32)
+    d["values"][r.random(len(d["values"])) < 0.1] = np.nan
+    cuts, _, _, page = oracle_quantize(d, 2)
+    ctx = gbt.Context(0)
+    mx = gbt.gbt_quantize(ctx, d, max_bin=2)
+    cp, cv = mx.cuts()
+    assert same_bits(cp, cuts.cut_ptr) and same_bits(cv, cuts.cut_values)
+    assert same_bits(mx.page(0), page)
+    ctx.close()
+
+
 def test_csr_without_room_for_the_count_tables(gbt):
     """A budget that holds the pairs, the grouped keys and 8 bytes per
     feature, but not the grouping's count tables (98 blocks x 2000 features)."""
