@@ -250,12 +250,12 @@ gbt_status gbt_ctx_create(int32_t device, uint64_t budget_bytes, void *hip_strea
  * it. */
 gbt_status gbt_ctx_destroy(gbt_ctx *ctx);
 /* Bytes of device memory requested for the context's objects and workspaces,
- * now and at most (what a budget counts).  Not in it: a context without a
- * budget keeps blocks above 64 MiB that it has freed for its next
- * allocations (a kept block serves a request of at least four fifths of its
- * size; the request is counted).  They are at most 4 GiB on a device over all
- * contexts of the process, and are returned when an allocation of any
- * context on the device fails and when their context is destroyed. */
+ * now and at most (what a budget counts).  Not in it: blocks above 64 MiB
+ * that contexts without a budget have freed are kept for the next allocations
+ * of such contexts on the device (a kept block serves a request of at least
+ * four fifths of its size; the request is counted).  They are at most 4 GiB
+ * on a device in all, and are returned when an allocation of any context on
+ * the device fails and when the context that freed them is destroyed. */
 gbt_status gbt_ctx_memory(gbt_ctx *ctx, uint64_t *used_bytes, uint64_t *peak_bytes);
 /* HIP events on the context stream (gbt_tree_stats.ms_*): 0 off, 1 around
  * the histogram-building kernel only (with the evaluation where a level of

@@ -37,24 +37,26 @@ gbt_status set_device(gbt_ctx *c)
     return GBT_OK;
 }
 
-// Freed blocks above kSpareMin stay with a context without a byte budget, up
-// to kSpareMax on a device over all contexts of the process, and serve the
-// context's later allocations of at most their size and at least four fifths
-// of it.  The runtime returns such blocks to the driver, which clears them
+// Blocks above kSpareMin that contexts without a byte budget free are kept,
+// up to kSpareMax on a device, and serve later allocations of such contexts
+// on it of at most their size and at least four fifths of it.  The runtime returns such blocks to the driver, which clears them
 // before it hands them out again: once the card's memory has been through one
 // use, hipMalloc takes about 8 ms per GB (5 ms for 640 MB, 75-100 ms for 2 GB,
 // measured over 500 allocate-and-free pairs; 40 us while unused memory is
 // left), and a 10 M x 50 quantization, which needs 2.7 GB for 5 ms of kernels,
 // took 27 ms.  Blocks up to 64 MB come from the runtime's own pool (12 us).
 // An allocation that fails in any context returns the kept blocks of its
-// device first.
+// device first, and a context's end those that it freed.  The blocks are the
+// device's and not each context's: with a share of its own, four contexts
+// that took turns at that quantization would need four times the memory, or
+// pay 78 ms each for the others' blocks dropped at the bound.
 constexpr size_t kSpareMin = (size_t)64 << 20;
 constexpr size_t kSpareMax = (size_t)4 << 30;
 
 namespace {
 
 struct Spare {
-    const gbt_ctx *owner;
+    const gbt_ctx *from;  // the context that freed it
     int device;
     void *p;
     size_t bytes;
@@ -93,8 +95,8 @@ bool drop_spares(Take &&take)
     return !out.empty();
 }
 
-// The context's kept block that serves `bytes` best, out of the pool; p NULL
-// when there is none.
+// The kept block of the context's device that serves `bytes` best, out of the
+// pool; p NULL when there is none.
 gbt_ctx::Block take_spare(const gbt_ctx *c, size_t bytes)
 {
     SparePool &pool = spare_pool();
@@ -102,7 +104,7 @@ gbt_ctx::Block take_spare(const gbt_ctx *c, size_t bytes)
     size_t best = pool.blocks.size();
     for (size_t i = 0; i < pool.blocks.size(); ++i) {
         const Spare &b = pool.blocks[i];
-        if (b.owner == c && b.bytes >= bytes && b.bytes - b.bytes / 5 <= bytes &&
+        if (b.device == c->device && b.bytes >= bytes && b.bytes - b.bytes / 5 <= bytes &&
             (best == pool.blocks.size() || b.bytes < pool.blocks[best].bytes))
             best = i;
     }
@@ -405,7 +407,7 @@ gbt_status gbt_ctx_destroy(gbt_ctx *c)
     (void)hipStreamSynchronize(c->stream);
     (void)hipStreamSynchronize(c->side);
     for (auto &s : c->scratch) dev_free(c, s.p, s.bytes);
-    drop_spares([&](const Spare &s) { return s.owner == c; });
+    drop_spares([&](const Spare &s) { return s.from == c; });
     if (c->hio) (void)hipHostFree(c->hio);
     if (c->tres) (void)hipHostFree(c->tres);
     for (auto e : c->tres_ev) (void)hipEventDestroy(e);

@@ -191,7 +191,12 @@ def test_kept_blocks_are_bounded_over_contexts(gbt):
     ctxs = [gbt.Context(0) for _ in range(4)]
     for ctx in ctxs:  # 1.3 GB of keys and more each
         gbt.gbt_quantize(ctx, X).free()
-    assert before - free_bytes() < (4 << 30) + (256 << 20)
+        gbt.gbt_quantize(ctx, X[:len(X) // (1 + ctxs.index(ctx))]).free()  # of several sizes
+    held = before - free_bytes()
+    assert held < (4 << 30) + (256 << 20)
+    for ctx in ctxs:  # the contexts share the kept blocks
+        gbt.gbt_quantize(ctx, X).free()
+    assert before - free_bytes() < held + (64 << 20)
     for ctx in ctxs:
         ctx.close()
     assert before - free_bytes() < 256 << 20
