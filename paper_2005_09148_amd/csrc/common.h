@@ -94,6 +94,7 @@ struct gbt_ctx {
     void *hio = nullptr;
     void *hio_d = nullptr;
     size_t hio_bytes = 0;
+    int predictions = 0;  // calls that walked trees in LDS (counted up to where it matters)
     // pinned memory a tree's last kernels write the tree into (one slot per
     // tree of a run of trees whose results are read together), and events
     // recorded after trees whose slot is reused within a run

@@ -12,6 +12,7 @@ struct LdsTrees {
     const int32_t *depth = nullptr;   // depth of each tree
     int32_t n_chunks = 0;
     int32_t chunk_words = 0;          // words of the largest chunk
+    std::vector<char> host;           // what the upload reads, unless that is host_io's buffer
 };
 
 // Rows per block for the ensemble over n_rows rows of row_words 32-bit words
@@ -22,9 +23,9 @@ int32_t lds_predict_rows(const gbt_tree *trees, int32_t n_trees, int64_t n_rows,
 
 // Compacts the trees and uploads them.  w > 0: splits of binned rows with
 // w-bit symbols; w = 0: splits of raw values.  *ok is false (and nothing is
-// uploaded) when a split names no column of the n_cols.  The copy reads the
-// pinned buffer of host_io: the stream is to be synchronized before that
-// buffer's next use.
+// uploaded) when a split names no column of the n_cols.  The copy reads
+// out->host or the pinned buffer of host_io: the stream is to be synchronized
+// before the one is destroyed or the other used again.
 gbt_status lds_upload_trees(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, int32_t w, int32_t n_cols,
                             LdsTrees *out, bool *ok);
 

@@ -2080,7 +2080,17 @@ gbt_status gbt_predict(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, const
                                                         binned ? binned->row_words : raw->n_cols, binned != nullptr)
                                      : 0;
     LdsTrees lt;
+    // ends before lt does, on every way out
+    struct Drain {
+        hipStream_t stream;
+        bool queued;
+        ~Drain()
+        {
+            if (queued) (void)hipStreamSynchronize(stream);
+        }
+    } drain{c->stream, false};
     bool in_lds = block_rows > 0;
+    drain.queued = in_lds;
     if (in_lds)
         GBT_TRY(lds_upload_trees(c, trees, n_trees, binned ? binned->w : 0, binned ? binned->m : raw->n_cols, &lt,
                                  &in_lds));
@@ -2125,6 +2135,7 @@ gbt_status gbt_predict(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, const
             GBT_LAUNCHED();
         }
     }
+    drain.queued = false;
     GBT_HIP(hipStreamSynchronize(c->stream));
     return GBT_OK;
 }

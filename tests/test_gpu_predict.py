@@ -133,3 +133,40 @@ def test_wide_rows_cost_what_the_trees_read(gbt):
             best[what] = min(best[what], time.perf_counter() - t)
     assert best["predict"] < 3 * best["copy"]
     ctx.close()
+
+
+def test_first_and_later_calls_of_a_context(gbt):
+    """The first 16 calls' trees go up from ordinary memory, later ones from
+    pinned memory, and more than 4 MB of them from ordinary memory again."""
+    r = np.random.default_rng(8)
+    X = r.normal(size=(300, 9)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    ctx = gbt.Context(0)
+    few = ensemble(gbt, [6] * 12, 9, 8, 3)
+    more = ensemble(gbt, [8] * 40, 9, 8, 4)
+    large = ensemble(gbt, [11], 9, 8, 5) * 180  # 4.4 MB
+    for trees in (few, more, large) + (few,) * 13 + (more, few, large, more, few):
+        got = gbt.gbt_predict(ctx, trees, 0.5, raw=Xd)
+        assert got.cpu().numpy().tobytes() == walk(gbt, trees, X, 0.5).tobytes()
+    ctx.close()
+
+
+def test_first_call_takes_no_pinned_memory(gbt):
+    """A fresh context's first call against its next ones: 1.3 times as long;
+    with an allocation of pinned memory in it, 2.3 to 2.9."""
+    import time
+    X = torch.randn(1000, 28, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    trees = ensemble(gbt, [6] * 10, 28, 8, 1)
+    warm = gbt.Context(0)
+    gbt.gbt_predict(warm, trees, 0.0, raw=X)
+    first, later, ctxs = [], [], []
+    for _ in range(21):
+        ctxs.append(gbt.Context(0))
+        torch.cuda.synchronize()
+        for k in range(6):
+            t = time.perf_counter()
+            gbt.gbt_predict(ctxs[-1], trees, 0.0, raw=X)
+            (later if k else first).append(time.perf_counter() - t)
+    assert np.median(first) < 1.9 * np.median(later)
+    for c in ctxs + [warm]:
+        c.close()
