@@ -373,8 +373,14 @@ __device__ inline uint32_t sparse_symbol(const uint32_t *__restrict__ row, int32
 // the passes below the root took 82 us on average (2 M rows x 2000 features,
 // depth 10) and up to 226 us, now 71 us and at most 115 us.  A pass of fewer
 // items than XCDs deals the pairs instead, as whole items would leave XCDs
-// idle.  The row-id and slot-range chain does not bound a pass: with all of
-// it requested a row ahead it took the same time.
+// idle (one tree of 2000 x 20,000 at 400 values a row 1.31 against 1.45 ms),
+// and so does one of a single group, which has nothing to share.  The grid is
+// sized for the most work items a level can have, and a workgroup's LDS lets
+// one run on a CU at a time, so what an idle block does before it ends counts:
+// with the item's and group's records requested before the check a pass of
+// 60,000 rows took 20.2 us, with the count alone 14.2 (14.3 with pairs
+// throughout).  The row-id and slot-range chain does not bound a pass: with
+// all of it requested a row ahead it took the same time.
 template <bool kRows>
 __global__ void __launch_bounds__(kSparseThreads)
     k_hist_sparse(const uint32_t *__restrict__ page, int32_t row_words, int32_t w, uint32_t mask,
@@ -385,24 +391,17 @@ __global__ void __launch_bounds__(kSparseThreads)
                   const uint8_t *__restrict__ slot_tbl, int32_t tbl_stride)
 {
     extern __shared__ unsigned long long lds[];
-    const int32_t lb = (int32_t)(blockIdx.x / kXcds);
-    const int32_t item = lb / n_groups * kXcds + (int32_t)(blockIdx.x % kXcds);
-    int32_t gi = lb % n_groups;
-    // the records of a pass of at least kXcds items are requested with the
-    // count, not after it (item < max_work <= the list's room)
-    HistWork wk = work[min(item, max_work - 1)];
-    HistGroup gr = groups[gi];
-    const int32_t items = n_work_d ? *n_work_d : max_work;
-    if (items < kXcds) {
-        const uint32_t active = (uint32_t)(items * n_groups);
-        if (blockIdx.x >= active) return;
-        const uint32_t L = xcd_remap(blockIdx.x, active);
-        wk = work[L / n_groups];
-        gi = (int32_t)(L % n_groups);
-        gr = groups[gi];
-    } else if (item >= items) {
-        return;
-    }
+    const uint32_t items = (uint32_t)(n_work_d ? *n_work_d : max_work), G = (uint32_t)n_groups;
+    const bool deal = G > 1 && items >= kXcds;
+    // blocks past the pass's work end here (the grid is sized for the most)
+    const uint32_t active = (deal ? (items + kXcds - 1) / kXcds * kXcds : items) * G;
+    if (blockIdx.x >= active) return;
+    const uint32_t lb = deal ? blockIdx.x / kXcds : xcd_remap(blockIdx.x, active);
+    const uint32_t item = deal ? lb / G * kXcds + blockIdx.x % kXcds : lb / G;
+    const int32_t gi = (int32_t)(lb % G);
+    if (item >= items) return;
+    const HistWork wk = work[item];
+    const HistGroup gr = groups[gi];
     const int32_t nb = gr.b1 - gr.b0;
     unsigned long long *sg = lds, *sh = lds + nb;
     lds_zero(sg, sh, nb);
