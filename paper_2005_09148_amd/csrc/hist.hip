@@ -371,10 +371,13 @@ __device__ inline uint32_t sparse_symbol(const uint32_t *__restrict__ row, int32
 // Whole work items are dealt over the XCDs, so the groups of one item share
 // its L2 for the rows; with contiguous runs of (item, group) pairs per XCD
 // the passes below the root took 82 us on average (2 M rows x 2000 features,
-// depth 10) and up to 226 us, now 71 us and at most 115 us.  A pass of fewer
-// items than XCDs deals the pairs instead, as whole items would leave XCDs
-// idle (one tree of 2000 x 20,000 at 400 values a row 1.31 against 1.45 ms),
-// and so does one of a single group, which has nothing to share.  The grid is
+// depth 10) and up to 226 us, now 71 us and at most 115 us.  Where whole items
+// would leave XCDs idle for more than a fifth of the time (items short of a
+// multiple of eight; fewer than eight) a pass deals the pairs instead: one
+// tree of 581,202 x 3907 with one value a row 368 us, 484 with whole items in
+// every pass from eight (410 with pairs in every pass, before), of 1 M x 3000
+// with twenty 650, 710 (728), of 2000 x 20,000 with 400 1310, 1450 (1320);
+// so does one of a single group, which has nothing to share.  The grid is
 // sized for the most work items a level can have, and a workgroup's LDS lets
 // one run on a CU at a time, so what an idle block does before it ends counts:
 // with the item's and group's records requested before the check a pass of
@@ -392,9 +395,10 @@ __global__ void __launch_bounds__(kSparseThreads)
 {
     extern __shared__ unsigned long long lds[];
     const uint32_t items = (uint32_t)(n_work_d ? *n_work_d : max_work), G = (uint32_t)n_groups;
-    const bool deal = G > 1 && items >= kXcds;
+    const uint32_t up = (items + kXcds - 1) / kXcds * kXcds;
+    const bool deal = G > 1 && items >= kXcds && 4 * up <= 5 * items;
     // blocks past the pass's work end here (the grid is sized for the most)
-    const uint32_t active = (deal ? (items + kXcds - 1) / kXcds * kXcds : items) * G;
+    const uint32_t active = (deal ? up : items) * G;
     if (blockIdx.x >= active) return;
     const uint32_t lb = deal ? blockIdx.x / kXcds : xcd_remap(blockIdx.x, active);
     const uint32_t item = deal ? lb / G * kXcds + blockIdx.x % kXcds : lb / G;

@@ -136,10 +136,12 @@ def test_stats_name_the_root_kernel(n, forced, kind):
     ctx.close()
 
 
-@pytest.mark.parametrize("n,m,density", [(1500, 3000, 0.01), (14_000, 1500, 0.01), (40_000, 600, 0.02)])
+@pytest.mark.parametrize("n,m,density", [(1500, 3000, 0.01), (14_000, 1500, 0.01), (22_000, 1000, 0.01),
+                                         (40_000, 600, 0.02)])
 def test_sparse_passes_of_few_items_match_oracle(n, m, density):
     """Sparse passes with fewer work items than XCDs (2048 rows each), with
-    more, and of both in one tree, over several feature groups."""
+    more that are short of a multiple of eight or nearly one, and of several
+    kinds in one tree, over several feature groups."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from oracle import oracle as orc
