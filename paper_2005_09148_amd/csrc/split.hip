@@ -1252,7 +1252,13 @@ __global__ void __launch_bounds__(kPartThreads)
 // 500 of 32 bins) and 0.75 against 0.83 (256 bins), 4.1 M 0.88 against 0.81
 // (8192 x 500, 32 bins), 8.2 M 1.08 against 0.89 (16,384 x 500), 33 M 2.9
 // against 1.5 (16,384 x 2000); 1.0 M cells of 1000 columns 1.00 against 0.87,
-// of 500 columns 0.72 against 0.71 (32 bins).  (A partition by one block of 1024 threads, with the choice, the
+// of 500 columns 0.72 against 0.71 (32 bins).  On deep levels of many nodes
+// the blocks are more than the rows: the chunked passes then start fewer,
+// whose cost grows with the bins.  ms for two trees of depth 12, chunked
+// throughout / one kernel up to 8192 blocks a level / up to 65,536 / always:
+// 32 bins 4000 x 168 1.09, 0.99, 1.09, 1.26, 4000 x 500 1.70, 1.54, 1.75,
+// 2.37, 12,000 x 100 1.34, 1.23, 1.39, 1.49; 256 bins 4000 x 168 1.51, 1.28,
+// 1.20, 1.26, 4000 x 500 2.70, 2.10, 1.91, 2.01.  (A partition by one block of 1024 threads, with the choice, the
 // flags, the scatter and the plan in one kernel, took 21.6 us against 11.6 us
 // for the two kernels over all CUs.)
 template <bool kRows, int kT>
@@ -1371,6 +1377,8 @@ bool small_level_fits(const gbt_matrix *mx, int64_t R, int32_t level)
     // below the root a level's built nodes hold at most R / 2 rows in all
     if (mx->sparse || R <= 0 || R > (level ? 2 * kSmallRows : kSmallRows)) return false;
     if (mx->m > kSmallCols || R * mx->m > kSmallCells) return false;
+    // blocks (columns times built nodes) against the mean bins of a column
+    if (level && ((int64_t)mx->m * mx->m << (level - 1)) > kSmallBlocks * mx->total_bins) return false;
     for (int32_t f = 0; f < mx->m; ++f)
         if (mx->bin_ptr_h[f + 1] - mx->bin_ptr_h[f] > 256) return false;
     return true;

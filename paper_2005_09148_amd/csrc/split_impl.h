@@ -112,6 +112,7 @@ gbt_status partition_rev_impl(gbt_ctx *c, const gbt_matrix *mx, const uint32_t *
 constexpr int64_t kSmallRows = 16384;  // training rows up to which the root level takes it
 constexpr int64_t kSmallCells = (int64_t)1 << 21;  // training rows times columns, at every level
 constexpr int32_t kSmallCols = 512;                // columns
+constexpr int64_t kSmallBlocks = 256;              // columns times built nodes, per mean bin of a column
 // Whether that level of a tree of R training rows of mx takes it (dense
 // pages, features of at most 256 bins).
 bool small_level_fits(const gbt_matrix *mx, int64_t R, int32_t level);

@@ -1200,7 +1200,9 @@ static gbt_status train_tree_enqueue(gbt_ctx *c, const gbt_matrix *mx, const flo
         cols = cc;
     }
     int64_t *partials = nullptr;
-    if (!small_at(0))
+    bool chunked = D == 0;  // some level takes the chunked passes
+    for (int32_t d = 0; d < D; ++d) chunked = chunked || !small_at(d);
+    if (chunked)
         GBT_TRY(scratch(c, kScrPartialsDev, (size_t)std::max(max_items, 1) * mx->total_bins * 16, (void **)&partials));
     // the root's slot arrays only for a tree without levels (whose leaves
     // may be added at the slots' rows); the root level's partition takes

@@ -65,10 +65,11 @@ def test_small_levels(n, m, max_bin, depth, f, loss):
 
 
 @pytest.mark.parametrize("n,m,max_bin,depth", [(4096, 512, 16, 4), (4097, 512, 16, 4), (300, 512, 256, 3),
-                                               (300, 513, 256, 3)])
+                                               (300, 513, 256, 3), (900, 200, 16, 9), (700, 60, 40, 11)])
 def test_wide_small_trees_match_oracle(n, m, max_bin, depth):
     """Trees of few rows on both sides of the column and cell limits of the
-    one-kernel levels, bit for bit against the CPU oracle."""
+    one-kernel levels, and deep ones whose lower levels pass the limit on
+    their blocks, bit for bit against the CPU oracle."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from oracle import oracle as orc
@@ -80,29 +81,29 @@ def test_wide_small_trees_match_oracle(n, m, max_bin, depth):
     y = (np.nan_to_num(X[:, 1]) + r.normal(size=n) > 0).astype(np.float32)
     ctx = gbt.Context(0)
     trees, margin = gbt.train(ctx, gbt.gbt_quantize(ctx, X, max_bin=max_bin), torch.from_numpy(y).cuda(),
-                              gbt.make_train_params(loss=0, max_depth=depth, eta=0.3), 2, 0.0)
+                              gbt.make_train_params(loss=1, max_depth=depth, eta=0.3), 2, 0.0)
     _, b, _, _ = oracle_quantize(X, max_bin)
-    want, want_margin = orc.train(b, y, orc.Params(loss=0, max_depth=depth, eta=0.3), 2, 0.0)
+    want, want_margin = orc.train(b, y, orc.Params(loss=1, max_depth=depth, eta=0.3), 2, 0.0)
     for g, o in zip(trees, want):
         assert node_diff(g.nodes, o.nodes) is None
     assert margin.cpu().numpy().tobytes() == want_margin.tobytes()
     ctx.close()
 
 
-def test_wide_small_trees_take_no_longer():
-    """16,384 x 2000 rows: the chosen path takes no longer than the chunked
-    passes (one-kernel levels without a bound on the columns took 1.9 times
-    as long; 1.3 allows for the spread of one run)."""
+@pytest.mark.parametrize("n,m,depth", [(16_384, 2000, 6), (4000, 500, 12)])
+def test_wide_small_trees_take_no_longer(n, m, depth):
+    """The chosen path takes no longer than the chunked passes (one-kernel
+    levels took 1.9 times as long without a bound on the columns, 1.4 times
+    without one on a level's blocks; 1.2 allows for the spread of one run)."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import time
     from paper_2005_09148_amd import gbt
-    n, m = 16_384, 2000
     X = torch.randn(n, m, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
     y = (X[:, 0] > 0).float()
     ctx = gbt.Context(0)
     mx = gbt.gbt_quantize(ctx, X, max_bin=32)
-    P = gbt.make_train_params(loss=0, max_depth=6, eta=0.1)
+    P = gbt.make_train_params(loss=0, max_depth=depth, eta=0.1)
     best = {}
     for _ in range(6):
         for kernel in (ctx.HIST_AUTO, ctx.HIST_PLAIN):
@@ -112,7 +113,7 @@ def test_wide_small_trees_take_no_longer():
             t = time.perf_counter()
             gbt.gbt_train_trees(ctx, mx, y, margin, P, 3)
             best[kernel] = min(best.get(kernel, 1e9), time.perf_counter() - t)
-    assert best[ctx.HIST_AUTO] < 1.3 * best[ctx.HIST_PLAIN]
+    assert best[ctx.HIST_AUTO] < 1.2 * best[ctx.HIST_PLAIN]
     ctx.close()
 
 
