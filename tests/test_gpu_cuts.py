@@ -202,6 +202,44 @@ def test_kept_blocks_are_bounded_over_contexts(gbt):
     assert before - free_bytes() < 256 << 20
 
 
+def test_kept_blocks_between_threads_and_streams(gbt):
+    """Contexts on streams of their own, used by threads at the same time,
+    hand large blocks to one another: every page stays as one context alone
+    makes it."""
+    import threading
+    sizes = (2_700_000, 3_000_000, 2_500_000)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    data = [torch.randn(n, 28, generator=g, device="cuda") for n in sizes]
+    alone = gbt.Context(0, budget_bytes=64 << 30)  # keeps no blocks
+    want = []
+    for X in data:
+        mx = gbt.gbt_quantize(alone, X)
+        want.append((mx.cuts()[1].tobytes(), mx.page(0).tobytes()))
+        mx.free()
+    torch.cuda.synchronize()
+    wrong, errors = [], []
+
+    def work(k):
+        try:
+            ctx = gbt.Context(0, stream=torch.cuda.Stream())
+            for i in range(5):
+                mx = gbt.gbt_quantize(ctx, data[(k + i) % 3])
+                if (mx.cuts()[1].tobytes(), mx.page(0).tobytes()) != want[(k + i) % 3]:
+                    wrong.append((k, i))
+                mx.free()
+            ctx.close()
+        except Exception as e:  # shown below: a thread's exception would pass unseen
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors and not wrong
+    alone.close()
+
+
 def csr_rows(n, m, density, seed, nan=0.0, empty=0.0):
     r = np.random.default_rng(seed)
     lens = np.minimum(r.binomial(m, density, n), m)
