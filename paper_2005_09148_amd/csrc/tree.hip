@@ -1450,8 +1450,20 @@ static gbt_status train_tree_impl(gbt_ctx *c, const gbt_matrix *mx, const float 
     return train_tree_finish(c, pt, tree, stats);
 }
 
+// Waits for the stream when a call ends early whose host buffers queued
+// copies may still read.
+struct StreamDrain {
+    hipStream_t stream;
+    bool done = false;
+    ~StreamDrain()
+    {
+        if (!done) (void)hipStreamSynchronize(stream);
+    }
+};
+
+// The copy reads *host: it is to live until the stream is synchronized.
 static gbt_status upload_trees(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, gbt_node **nodes_d,
-                               int64_t **offs_d)
+                               int64_t **offs_d, std::vector<char> *host)
 {
     std::vector<int64_t> offs(n_trees + 1, 0);
     for (int32_t t = 0; t < n_trees; ++t) {
@@ -1461,7 +1473,8 @@ static gbt_status upload_trees(gbt_ctx *c, const gbt_tree *trees, int32_t n_tree
     size_t o_off = ((size_t)offs[n_trees] * sizeof(gbt_node) + 255) / 256 * 256;
     char *buf;
     GBT_TRY(scratch_t(c, kScrTrees, o_off + (n_trees + 1) * 8, &buf));
-    std::vector<char> h(o_off + (n_trees + 1) * 8);
+    std::vector<char> &h = *host;
+    h.resize(o_off + (n_trees + 1) * 8);
     for (int32_t t = 0; t < n_trees; ++t)
         memcpy(h.data() + offs[t] * sizeof(gbt_node), trees[t].nodes, trees[t].n_nodes * sizeof(gbt_node));
     memcpy(h.data() + o_off, offs.data(), (n_trees + 1) * 8);
@@ -2023,7 +2036,9 @@ gbt_status gbt_update_leaves(gbt_ctx *c, gbt_tree *tree, const gbt_train_params 
     GBT_TRY(set_device(c));
     gbt_node *nodes_d;
     int64_t *offs_d;
-    GBT_TRY(upload_trees(c, tree, 1, &nodes_d, &offs_d));
+    std::vector<char> host;
+    StreamDrain drain{c->stream};
+    GBT_TRY(upload_trees(c, tree, 1, &nodes_d, &offs_d, &host));
     k_leaf_values<<<blocks(tree->n_nodes), 256, 0, c->stream>>>(nodes_d, tree->n_nodes, tree->exp_g,
                                                                tree->exp_h, tp->lambda, tp->eta);
     GBT_LAUNCHED();
@@ -2059,6 +2074,7 @@ gbt_status gbt_update_leaves(gbt_ctx *c, gbt_tree *tree, const gbt_train_params 
                            c->stream));
     unsigned long long n_bad = 0;
     if (bad) GBT_HIP(hipMemcpyAsync(&n_bad, bad, sizeof(n_bad), hipMemcpyDeviceToHost, c->stream));
+    drain.done = true;
     GBT_HIP(hipStreamSynchronize(c->stream));
     GBT_CHECK(n_bad == 0,
               "%llu of %lld positions name no leaf of the tree or no new row of the data (those rows were "
@@ -2082,21 +2098,12 @@ gbt_status gbt_predict(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, const
                                                         binned ? binned->row_words : raw->n_cols, binned != nullptr)
                                      : 0;
     LdsTrees lt;
-    // ends before lt does, on every way out
-    struct Drain {
-        hipStream_t stream;
-        bool queued;
-        ~Drain()
-        {
-            if (queued) (void)hipStreamSynchronize(stream);
-        }
-    } drain{c->stream, false};
+    StreamDrain drain{c->stream};  // ends before lt does, on every way out
     bool in_lds = block_rows > 0;
-    drain.queued = in_lds;
     if (in_lds)
         GBT_TRY(lds_upload_trees(c, trees, n_trees, binned ? binned->w : 0, binned ? binned->m : raw->n_cols, &lt,
                                  &in_lds));
-    if (n_trees && !in_lds) GBT_TRY(upload_trees(c, trees, n_trees, &nodes_d, &offs_d));
+    if (n_trees && !in_lds) GBT_TRY(upload_trees(c, trees, n_trees, &nodes_d, &offs_d, &lt.host));
     if (binned) {
         GBT_CHECK(binned->n_rows == 0 || margin_out_d, "output is NULL");
         Geo geo = geo_of(binned);
@@ -2137,7 +2144,7 @@ gbt_status gbt_predict(gbt_ctx *c, const gbt_tree *trees, int32_t n_trees, const
             GBT_LAUNCHED();
         }
     }
-    drain.queued = false;
+    drain.done = true;
     GBT_HIP(hipStreamSynchronize(c->stream));
     return GBT_OK;
 }
