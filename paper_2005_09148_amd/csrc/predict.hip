@@ -221,11 +221,13 @@ bool compact_tree(const gbt_tree &t, int32_t depth, int32_t w, int32_t n_cols, u
 // 234 at 12 (256 rows a block); 90 columns 467 / 234 at 12 and 560 / 550 at
 // 30, 120 columns 871 / 560 at 30 and 916 / 1021 at 60, 300 columns 7928 /
 // 3079 at 180 and 9621 / 10053 at 600, 480 columns 11424 / 75 at 3 (64 rows a
-// block).  30,000 rows: 120 columns 39 / 33 at 12 and 44 / 52 at 30, 200
-// columns 78 / 81 at 60, 480 columns 331 / 240 at 180 and 465 / 740 at 600; up
-// to 8 steps a walk in global memory ends as soon (26 / 26 at 28 columns and 6
-// steps).  Binned rows take 16-byte loads: 1 M rows of 76 words 114 / 125 at 6
-// steps, of 120 words 281 / 235 at 12 and 301 / 554 at 30.
+// block); 640,000 of 53 columns 119 / 110 at 8.  30,000 rows: 120 columns
+// 39 / 33 at 12 and 44 / 52 at 30, 200 columns 78 / 81 at 60, 480 columns 331 /
+// 240 at 180 and 465 / 740 at 600; few steps in global memory end as soon
+// (26 / 26 at 28 columns and 6 steps; 195 rows of 53 columns 36 / 32 at 12;
+// 1.4 M rows of 13 columns 46 / 43 at 2).
+// Binned rows take 16-byte loads: 1 M rows of 76 words 114 / 125 at 6 steps, of
+// 120 words 281 / 235 at 12 and 301 / 554 at 30.
 int32_t lds_predict_rows(const gbt_tree *trees, int32_t n_trees, int64_t n_rows, int32_t row_words, bool binned)
 {
     int32_t chunk = kChunkWords;
@@ -243,8 +245,9 @@ int32_t lds_predict_rows(const gbt_tree *trees, int32_t n_trees, int64_t n_rows,
     const int32_t rows = !few && lds_bytes(chunk, row_words, 256) <= kLdsRows256 ? 256
                          : lds_bytes(chunk, row_words, 64) <= kLdsRows64         ? 64
                                                                                  : 0;
-    const int64_t k = (few || rows == 256 ? 400 : 150) * (binned ? 4 : 1);
-    if (k * steps < (int64_t)row_words * row_words || (few && !binned && steps < 8)) return 0;
+    const int64_t k = (few ? 400 : rows == 256 ? 300 : 150) * (binned ? 4 : 1);
+    if (k * steps < (int64_t)row_words * row_words) return 0;
+    if (steps < (!few ? 4 : binned ? 6 : 8 + row_words / 6)) return 0;
     return rows;
 }
 

@@ -73,8 +73,9 @@ def test_predict_matches_walk(gbt, n, m, depths, cut, kind):
 
 
 @pytest.mark.parametrize("n,m,depths", [
-    (400, 90, [4] * 5), (400, 90, [4] * 4 + [5]), (33_000, 40, [3]), (33_000, 40, [4]), (33_000, 5, [0, 1, 2, 0]),
-    (33_000, 90, [6] * 9), (33_000, 90, [5, 6] * 5), (300, 480, [8] * 72), (500, 28, [7]), (500, 28, [4, 4])])
+    (400, 90, [4] * 5 + [2]), (400, 90, [4] * 5 + [3]), (33_000, 40, [5]), (33_000, 40, [6]),
+    (33_000, 5, [0, 1, 3, 0]), (33_000, 5, [0, 1, 2, 0]), (33_000, 90, [6] * 9), (33_000, 90, [6] * 8 + [5]), (300, 480, [8] * 72),
+    (500, 28, [4] * 3), (500, 28, [5, 4, 4]), (500, 28, [5]), (500, 28, [6])])
 @pytest.mark.parametrize("kind", ["raw", "binned"])
 def test_predict_around_the_step_rule(gbt, n, m, depths, kind):
     """Both sides of the line in steps from which rows are staged in LDS."""
